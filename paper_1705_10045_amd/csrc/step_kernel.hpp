@@ -42,21 +42,20 @@ namespace lbm {
 
 // XCD-aware placement.  Consecutive workgroups are dealt round-robin to the 8 XCDs, and a launch
 // larger than what the GPU holds at once runs in rounds of `resident` workgroups (dispatched in
-// index order as earlier ones retire).  Workgroup b of round r = b / resident is given logical
-// tile r * resident + (b % 8) * (resident / 8) + (b % resident) / 8, so that
+// index order as earlier ones retire).  The workgroups of one round that XCD x gets are given
+// consecutive logical tiles, behind those of XCD x - 1 (a round of any length: the first
+// cnt % 8 XCDs hold one workgroup more), so that
 //   - each round covers one contiguous run of tiles (x fastest, then y: a band of tile rows),
 //     and every tile's neighbours inside the band run at the same time as it;
 //   - each XCD owns a contiguous part of that run, and shared halos meet in its own L2.
-// A last round shorter than `resident` is split the same way when it is a multiple of 8 and
-// left in index order otherwise.  resident <= 0 means one round (the whole launch).
+// resident <= 0 means one round (the whole launch).
 __device__ __forceinline__ int xcd_logical_block(int b, int nblk, int resident = 0)
 {
     const int R = (resident > 0 && resident < nblk && (resident & 7) == 0) ? resident : nblk;
     const int base = (b / R) * R;
     const int cnt = min(R, nblk - base);
-    if ((cnt & 7) != 0) return b;
-    const int l = b - base;
-    return base + (l & 7) * (cnt >> 3) + (l >> 3);
+    const int l = b - base, x = l & 7;
+    return base + x * (cnt >> 3) + min(x, cnt & 7) + (l >> 3);
 }
 
 // Interior-first enumeration of a (W+2h) x (H+2h) region around a W x H tile: slots
