@@ -417,6 +417,73 @@ void choose_geometry(lbm_sim* s, int chunk_request)
     s->tile_y = ty;
 }
 
+// Tiles and z chunks of the collision launch of the two-launch step (split_kernel.hpp).  Its
+// workgroups are small and several run on a CU, so chunks are short: one plane while all tiles
+// of all planes run at once (an idle chip is bound by the chain of one workgroup: 32^3 takes
+// 10.4 us with chunks of 1, 12.6 with 2, 17.4 with 4), two up to eight rounds (96^3: 85.6, 82.3,
+// 84.8 us), then four, whose extra planes no longer matter (160^3: 410, 382, 370 us; 8: 369).
+StepGeom split_geometry(const lbm_params& p, int cus)
+{
+    int tx, ty;
+    split_tile(tx, ty);
+    StepGeom g{};
+    g.nx = p.nx; g.ny = p.ny; g.nz = p.nz;
+    g.pitch = row_pitch(p.nx, p.storage_bytes);
+    g.plane = padded_plane(plane_elements(p));
+    g.ntx = (p.nx + tx - 1) / tx;
+    g.nty = (p.ny + ty - 1) / ty;
+    const int per_cu = p.storage_bytes == 4 ? 3 : 2;   // by registers: 168 and 256 VGPRs
+    const long long tiles = (long long)g.ntx * g.nty * p.nz, round = (long long)cus * per_cu;
+    g.resident = (int)round;
+    g.chunk = tiles <= round ? 1 : (tiles <= 8 * round ? 2 : 4);
+    if (g.chunk > p.nz) g.chunk = p.nz;
+    g.nchunks = (p.nz + g.chunk - 1) / g.chunk;
+    return g;
+}
+
+// The two-launch step covers D3Q19 states under 4 GB (one buffer resource).
+bool split_covers(const lbm_params& p) { return p.lattice == 19 && state_bytes(p) < (1ull << 32); }
+
+// Whether the default step of these parameters runs as two launches: where their estimated time
+// is at least 5% below that of the fused launch.  Both estimates follow the measured times over
+// 18 boxes from 32^3 to 220x180x200 (within 10%, mostly within 5%):
+//   - two launches: 5 us and, per lane of the padded 32 x 8 tiles, 92 / 106 / 111 ps for FP32 with
+//     tau = 1 / other tau / MRT and 168 / 192 / 196 ps for FP64;
+//   - fused: rounds of resident workgroups times (chunk + 4) planes of 9.4 / 9.9 / 10.4 us for
+//     FP32 and 11.9 / 10.6 / 11.0 us for FP64, whatever the tiles' idle lanes.
+// So small boxes, whose fused launch is a few workgroups or a long chain, and ragged ones go
+// through two launches (FP32: 32^3 40.8 -> 10.4 us, 64^3 49.2 -> 24.1, 100^3 142 -> 118,
+// 200x150x97 330 -> 303; FP64: 128^3 457 -> 347), and the fused launch keeps the boxes that fill
+// its rounds, where it moves fewer bytes (128^3 FP32: 191 against 203 us).
+bool split_default(const lbm_params& p, const StepGeom& fused, const StepGeom& split, int cus, int per_cu)
+{
+    if (!split_covers(p)) return false;
+    const int kind = p.collision == LBM_COLLISION_MRT ? 2 : (p.tau == 1.0 ? 0 : 1);
+    static const double lane_ps[2][3] = {{92, 106, 111}, {168, 192, 196}};
+    static const double plane_us[2][3] = {{9.4, 9.9, 10.4}, {11.9, 10.6, 11.0}};
+    const int wide = p.storage_bytes == 8;
+    int tx, ty;
+    split_tile(tx, ty);
+    const double lanes = (double)split.ntx * tx * split.nty * ty * p.nz;
+    const double two = 5.0 + 1e-6 * lane_ps[wide][kind] * lanes;
+    const long long round = (long long)cus * per_cu;
+    const long long rounds = (step_workgroups(fused) + round - 1) / round;
+    return two < 0.95 * (double)rounds * (fused.chunk + 4) * plane_us[wide][kind];
+}
+
+// The scratch of the two-launch step: a workspace, not state.  False without room for it.
+bool ensure_split(lbm_sim* s)
+{
+    if (s->d_split) return true;
+    if (!split_covers(s->p)) return false;
+    s->split_geom = split_geometry(s->p, s->cus);
+    if (hipMalloc(&s->d_split, split_scratch_bytes(s->p.storage_bytes, plane_elements(s->p))) == hipSuccess)
+        return true;
+    (void)hipGetLastError();
+    s->d_split = nullptr;
+    return false;
+}
+
 lbm_status upload_table(lbm_sim* s)
 {
     const MaxwellTable& t = maxwell_table();
@@ -437,8 +504,17 @@ lbm_status enqueue_steps(lbm_sim* s, int nsteps)
         return LBM_EDEVICE;
     }
     for (int i = 0; i < nsteps; ++i) {
-        hipError_t e = launch_step(s->p.lattice, s->p.storage_bytes, s->variant, s->buf[s->cur],
-                                   s->buf[1 - s->cur], s->geom, s->phys, s->aux, s->stream);
+        hipError_t e;
+        if (s->split) {
+            e = launch_split_moments(s->p.storage_bytes, s->buf[s->cur], s->d_split, s->split_geom, s->phys,
+                                     s->aux, s->stream);
+            if (e == hipSuccess)
+                e = launch_split_collide(s->p.storage_bytes, s->buf[s->cur], s->buf[1 - s->cur], s->d_split,
+                                         s->split_geom, s->phys, s->aux, s->stream);
+        } else {
+            e = launch_step(s->p.lattice, s->p.storage_bytes, s->variant, s->buf[s->cur],
+                            s->buf[1 - s->cur], s->geom, s->phys, s->aux, s->stream);
+        }
         if (e != hipSuccess) return hip_fail(e, "step launch");
         s->cur ^= 1;
         s->step += 1;
@@ -551,6 +627,12 @@ lbm_status lbm_init(const lbm_params* params, const double* rho0, const double* 
     s->red_blocks = reduce_blocks(s->n);
     if (e == hipSuccess) e = hipMalloc((void**)&s->d_partials, sizeof(double) * (5 * s->red_blocks + 8));
     if (e != hipSuccess) { lbm_status r = hip_fail(e, "hipMalloc(state)"); lbm_free(s); return r; }
+    {
+        int tx, ty, per_cu;
+        step_tile(s->p.lattice, s->p.storage_bytes, s->variant, tx, ty, per_cu);
+        // without room for its scratch the fused step runs instead
+        s->split = split_default(s->p, s->geom, split_geometry(s->p, s->cus), s->cus, per_cu) && ensure_split(s);
+    }
     s->aux.err = s->d_err;
     e = hipMemsetAsync(s->d_err, 0, sizeof(int) * 16, s->stream);
     // zero padding so checkpoints are deterministic
@@ -627,6 +709,8 @@ lbm_status lbm_set_launch(lbm_sim* s, int variant, int chunk)
         return LBM_EINVAL;
     }
     s->variant = variant;
+    s->split = false;   // a launch of the fused step was asked for
+    s->launch_set = true;
     choose_geometry(s, chunk);
     return LBM_OK;
 }
@@ -729,7 +813,11 @@ lbm_status lbm_step_reduce(lbm_sim* s, int nsteps, double out[5])
     lbm_status st = enqueue_steps(s, nsteps - 1);
     if (st != LBM_OK) return st;
     // the last step's partial totals (5 per workgroup) and the totals, grown on demand
-    const long long wg = step_workgroups(s->geom);
+    // without a launch chosen by the caller, the last step runs as two launches wherever they apply:
+    // their totals cost a few per cent, the fused form's a fifth (128^3: 223 us against 190)
+    const bool split = !s->launch_set && ensure_split(s);
+    const StepGeom& geom = split ? s->split_geom : s->geom;
+    const long long wg = step_workgroups(geom);
     if (5 * wg + 8 > s->step_partials_len) {
         if (s->d_step_partials) {
             hipError_t e = hipFree(s->d_step_partials);
@@ -744,8 +832,16 @@ lbm_status lbm_step_reduce(lbm_sim* s, int nsteps, double out[5])
     double* d_out = s->d_step_partials + 5 * wg;
     StepAux aux = s->aux;
     aux.partials = s->d_step_partials;
-    hipError_t e = launch_step_totals(s->p.lattice, s->p.storage_bytes, s->variant, s->buf[s->cur],
-                                      s->buf[1 - s->cur], s->geom, s->phys, aux, d_out, s->stream);
+    hipError_t e;
+    if (split) {
+        e = launch_split_moments(s->p.storage_bytes, s->buf[s->cur], s->d_split, geom, s->phys, aux, s->stream);
+        if (e == hipSuccess)
+            e = launch_split_collide_totals(s->p.storage_bytes, s->buf[s->cur], s->buf[1 - s->cur], s->d_split,
+                                            geom, s->phys, aux, d_out, s->stream);
+    } else {
+        e = launch_step_totals(s->p.lattice, s->p.storage_bytes, s->variant, s->buf[s->cur],
+                               s->buf[1 - s->cur], geom, s->phys, aux, d_out, s->stream);
+    }
     if (e == hipErrorNotSupported) {
         // a launch variant without the fused form: the plain step, then the separate reduction
         st = enqueue_steps(s, 1);
@@ -830,6 +926,7 @@ lbm_status lbm_free(lbm_sim* s)
     if (s->d_step_partials) (void)hipFree(s->d_step_partials);
     if (s->d_table) (void)hipFree(s->d_table);
     if (s->d_scratch) (void)hipFree(s->d_scratch);
+    if (s->d_split) (void)hipFree(s->d_split);
     if (s->d_eos_p) (void)hipFree(s->d_eos_p);
     if (s->d_eos_coex) (void)hipFree(s->d_eos_coex);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);

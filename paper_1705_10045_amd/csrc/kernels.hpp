@@ -40,6 +40,19 @@ hipError_t launch_step(int Q, int storage_bytes, int variant, const void* src, v
 hipError_t launch_step_totals(int Q, int storage_bytes, int variant, const void* src, void* dst,
                               const StepGeom& g, const Phys& ph, const StepAux& aux, double* out,
                               hipStream_t st);
+// The two-launch D3Q19 step (split_kernel.hpp) on states under 4 GB: the moments of src into
+// `scratch` (split_scratch_bytes for plane_nodes = pitch * ny * nz elements), then the collision
+// launch on the tiles of split_tile; the second form also sums the totals of the state it writes
+// into aux.partials (5 per workgroup) and then into out[5].
+size_t split_scratch_bytes(int storage_bytes, long long plane_nodes);
+void split_tile(int& tx, int& ty);
+hipError_t launch_split_moments(int storage_bytes, const void* src, void* scratch, const StepGeom& g,
+                                const Phys& ph, const StepAux& aux, hipStream_t st);
+hipError_t launch_split_collide(int storage_bytes, const void* src, void* dst, const void* scratch,
+                                const StepGeom& g, const Phys& ph, const StepAux& aux, hipStream_t st);
+hipError_t launch_split_collide_totals(int storage_bytes, const void* src, void* dst, const void* scratch,
+                                       const StepGeom& g, const Phys& ph, const StepAux& aux, double* out,
+                                       hipStream_t st);
 // workgroups of one step launch (the entries of aux.partials it writes)
 inline long long step_workgroups(const StepGeom& g) { return (long long)g.ntx * g.nty * g.nchunks; }
 // Row pitch of the population planes: x rows padded to whole 128-byte lines, so that rows of

@@ -10,6 +10,15 @@
 
 namespace lbm {
 
+// The value itself, opaque to the compiler: a product that goes through it is rounded before it is
+// used (no contraction of it with a later sum), as one that goes through memory is.
+template <class R>
+__device__ __forceinline__ R rounded(R x)
+{
+    asm("" : "+v"(x));
+    return x;
+}
+
 // rho = sum N_k, j = sum c_k N_k, E = sum g_k (eq:hydro, section 4), summed in FP64 in direction
 // order (exact for FP32 populations up to the final rounding).  The density sums come first:
 // their populations may have been loaded earlier than the energy populations.
@@ -69,7 +78,7 @@ __device__ __forceinline__ void force_at(const double* pm, const double* p0, con
         const double* slm = L::cz[k] == 0 ? p0 : (L::cz[k] == 1 ? pm : pp);
         const double a = slp[e + L::cx[k] + W * L::cy[k]];
         const double b = slm[e - L::cx[k] - W * L::cy[k]];
-        double d = a * fma(A, a, Bm) - b * fma(A, b, Bm);
+        double d = fma(a, fma(A, a, Bm), -(b * fma(A, b, Bm)));
         if (force_coef<Q>(k) != 1.0) d *= force_coef<Q>(k);
         if (L::cx[k] == 1) fx += d; else if (L::cx[k] == -1) fx -= d;
         if (L::cy[k] == 1) fy += d; else if (L::cy[k] == -1) fy -= d;
@@ -80,25 +89,51 @@ __device__ __forceinline__ void force_at(const double* pm, const double* p0, con
     Fz = fz * inv_alpha;
 }
 
-// Energy source dE of sections 4-6 at index e of planes of row width W: pressure work
-// -p div u*, conservative conduction with face conductivity c_V chi (rho_i + rho_j)/2, and the
-// latent-heat term inside the coexistence band.  r0 and t0 are the rho and T planes of the
-// node; rm, tm and rp, tp the values of its neighbours at z - 1 and z + 1 (D = 3).
+// Pressure work -p div u* and conservative conduction with face conductivity
+// c_V chi (rho_i + rho_j)/2 (sections 4 and 6.2) at index e of planes of row width W.  r0 and t0
+// are the rho and T planes of the node; rm, tm and rp, tp the values of its neighbours at z - 1
+// and z + 1 (D = 3).
+template <int D, class R, int W>
+__device__ __forceinline__ R work_conduction(R p, R div, R rho, R rm, const R* r0, R rp, R tm, const R* t0,
+                                             R tp, int e, R cond_half, unsigned flags)
+{
+    // the contractions are written out: every launch form has to round them alike
+    R dE = R(0);
+    if (flags & kWork) dE = -(p * div);
+    if (flags & kConduction) {
+        const R Tc = t0[e];
+        R acc = fma(rho + r0[e + 1], t0[e + 1] - Tc, -((rho + r0[e - 1]) * (Tc - t0[e - 1])));
+        acc = fma(rho + r0[e + W], t0[e + W] - Tc, acc);
+        acc = fma(-(rho + r0[e - W]), Tc - t0[e - W], acc);
+        if constexpr (D == 3) {
+            const R z = fma(rho + rp, tp - Tc, -((rho + rm) * (Tc - tm)));
+            acc = acc + z;
+        }
+        dE = fma(cond_half, acc, dE);
+    }
+    return dE;
+}
+
+// The latent-heat term of section 5 for a node inside the band r1 < rho < r2, taken from dE.
+template <class R>
+__device__ __forceinline__ void latent_term(R& dE, double r1, double r2, R rho, R div, const Phys& ph)
+{
+    const double rd = double(rho);
+    if (rd > r1 && rd < r2) {
+        const double c = ph.rhoQ / (r2 - r1) * rd;
+        if constexpr (sizeof(R) == 8) dE = fma(-c, double(div), dE);
+        else dE -= R(c * double(div));
+    }
+}
+
+// Energy source dE of sections 4-6: work, conduction (see work_conduction) and the latent-heat
+// term inside the coexistence band.
 template <int D, class R, int W, bool TABLE = false>
 __device__ __forceinline__ R energy_source(R p, R div, R rho, R T, R rm, const R* r0, R rp,
                                            R tm, const R* t0, R tp, int e, R cond_half,
                                            unsigned flags, const Phys& ph, const StepAux& aux)
 {
-    R dE = R(0);
-    if (flags & kWork) dE -= p * div;
-    if (flags & kConduction) {
-        const R Tc = t0[e];
-        R acc = (rho + r0[e + 1]) * (t0[e + 1] - Tc) - (rho + r0[e - 1]) * (Tc - t0[e - 1]) +
-                (rho + r0[e + W]) * (t0[e + W] - Tc) - (rho + r0[e - W]) * (Tc - t0[e - W]);
-        if constexpr (D == 3)
-            acc += (rho + rp) * (tp - Tc) - (rho + rm) * (Tc - tm);
-        dE += cond_half * acc;
-    }
+    R dE = work_conduction<D, R, W>(p, div, rho, rm, r0, rp, tm, t0, tp, e, cond_half, flags);
     if (flags & kLatent) {
         const double Te = (flags & kBaro) ? ph.T0_baro : double(T);
         double r1, r2;
@@ -107,10 +142,7 @@ __device__ __forceinline__ R energy_source(R p, R div, R rho, R T, R rm, const R
             band = table_band(Te * ph.inv_T_c, ph, aux.eos_coex, r1, r2);
         else
             band = band_limits(Te * ph.inv_T_c, aux.maxwell, aux.tab_s0, aux.tab_inv_ds, ph.rho_c, r1, r2);
-        if (band) {
-            const double rd = double(rho);
-            if (rd > r1 && rd < r2) dE -= R(ph.rhoQ / (r2 - r1) * rd * double(div));
-        }
+        if (band) latent_term(dE, r1, r2, rho, div, ph);
     }
     return dE;
 }
@@ -178,6 +210,26 @@ __host__ __device__ constexpr double mrt_norm2(int i)
     return s;
 }
 
+// c_k . v over the nonzero components only (at most two): without fast-math rules the compiler
+// keeps the multiplications by zero, two instructions per direction and velocity.  `last(c, a, s)`
+// adds c times component a to s with the rounding of its choice.
+template <int Q, class R, class F>
+__device__ __forceinline__ R dot_c(int k, R x, R y, R z, F last)
+{
+    using L = Lattice<Q>;
+    const R v[3] = {x, y, z};
+    const int c[3] = {L::cx[k], L::cy[k], L::cz[k]};
+    R s = R(0);
+    bool any = false;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        if (c[a] == 0) continue;
+        s = any ? last(c[a], a, s) : (c[a] > 0 ? v[a] : -v[a]);
+        any = true;
+    }
+    return s;
+}
+
 // Both collisions of one node as linear combinations of the equilibrium polynomials
 // P_k(v) = w_k (1 + 3 c.v + 4.5 (c.v)^2 - 1.5 v^2) (eq:feq):
 //   N'_k = rho P_k(v) - keepN rho P_k(u) + keepN N_k             (eq:lbe, eq:edm)
@@ -195,19 +247,24 @@ template <int Q, class S, class R, bool WN, bool MRT = false>
 struct NodeCollision {
     static_assert(!MRT || WN, "the MRT collision reads N_k");
     static constexpr int NG = MRT ? MrtRows<Q>::N : 1;
+    R jx, jy, jz, inv_rho;               // u = j inv_rho
     R ux, uy, uz, vx, vy, vz, base_u, base_v, rho, keepN, nU, gV, gU, gK;
     R am[NG];
     double sumN, sumG;
 
-    __device__ __forceinline__ void setup(R rho_, R E, R ux_, R uy_, R uz_, R Fx, R Fy, R Fz,
-                                          R inv_rho, R dE, R keepN_, R keepG, R omega_E,
+    // The roundings of u, v and their products with c_k are written out, so that every launch
+    // form computes the same bits whatever the compiler would contract around it.
+    __device__ __forceinline__ void setup(R rho_, R E, R jx_, R jy_, R jz_, R Fx, R Fy, R Fz,
+                                          R inv_rho_, R dE, R keepN_, R keepG, R omega_E,
                                           bool pseudo)
     {
         rho = rho_;
-        ux = ux_; uy = uy_; uz = uz_;
-        vx = ux + Fx * inv_rho; vy = uy + Fy * inv_rho; vz = uz + Fz * inv_rho;
-        const R uu = ux * ux + uy * uy + uz * uz;
-        const R vv = vx * vx + vy * vy + vz * vz;
+        jx = jx_; jy = jy_; jz = jz_;
+        inv_rho = inv_rho_;
+        ux = jx * inv_rho; uy = jy * inv_rho; uz = jz * inv_rho;
+        vx = fma(Fx, inv_rho, ux); vy = fma(Fy, inv_rho, uy); vz = fma(Fz, inv_rho, uz);
+        const R uu = fma(uz, uz, fma(ux, ux, uy * uy));
+        const R vv = fma(vz, vz, fma(vy, vy, vx * vx));
         base_u = R(1) - R(1.5) * uu;
         base_v = R(1) - R(1.5) * vv;
         keepN = keepN_;
@@ -217,6 +274,19 @@ struct NodeCollision {
         gK = keepG + dE / E;
         sumN = 0.0;
         sumG = 0.0;
+    }
+
+    // c_k . u, the second component unrounded ((-1, -1, 0): the first), and c_k . v
+    __device__ __forceinline__ R dot_u(int k) const
+    {
+        if (Lattice<Q>::cx[k] == -1 && Lattice<Q>::cy[k] == -1) return fma(-jx, inv_rho, -uy);
+        const R j[3] = {jx, jy, jz};
+        return dot_c<Q>(k, ux, uy, uz, [&](int c, int a, R s) { return fma(c > 0 ? j[a] : -j[a], inv_rho, s); });
+    }
+    __device__ __forceinline__ R dot_v(int k) const
+    {
+        const R v[3] = {vx, vy, vz};
+        return dot_c<Q>(k, vx, vy, vz, [&](int c, int a, R s) { return c > 0 ? s + v[a] : s - v[a]; });
     }
 
     // MRT: the rows' moments of the non-equilibrium part f_k = N_k - rho P_k(u) over the moving
@@ -233,7 +303,7 @@ struct NodeCollision {
 #pragma unroll
             for (int k = 1; k < Q; ++k) {
                 const R w = R(weight<Q>(k));
-                const R cu = R(L::cx[k]) * ux + R(L::cy[k]) * uy + R(L::cz[k]) * uz;
+                const R cu = dot_u(k);
                 const R P = fma(R(4.5) * w, cu * cu, w * base_u) + R(3) * w * cu;
                 const R f = fma(-rho, P, pk_n[k]);
 #pragma unroll
@@ -255,8 +325,8 @@ struct NodeCollision {
         using L = Lattice<Q>;
         const int ko = opposite<Q>(k);
         const R w = R(weight<Q>(k));
-        const R cu = R(L::cx[k]) * ux + R(L::cy[k]) * uy + R(L::cz[k]) * uz;
-        const R cv = R(L::cx[k]) * vx + R(L::cy[k]) * vy + R(L::cz[k]) * vz;
+        const R cu = dot_u(k);
+        const R cv = dot_v(k);
         const R eu = fma(R(4.5) * w, cu * cu, w * base_u), ou = R(3) * w * cu;
         const R ev = fma(R(4.5) * w, cv * cv, w * base_v), ov = R(3) * w * cv;
         const R Pu[2] = {eu + ou, eu - ou}, Pv[2] = {ev + ov, ev - ov};

@@ -103,26 +103,42 @@ __host__ __device__ inline bool table_band(double Tr, const Phys& p,
     return true;
 }
 
-// Coexistence densities (rho_1, rho_2) of the band at reduced temperature Tr, cubic Lagrange
-// interpolation in s = sqrt(1 - Tr) on the FP64 Maxwell table (tab[2i] vapour, tab[2i+1]
-// liquid, reduced densities).  Returns false outside [kLatentTmin, kLatentTmax).
+// Position of reduced temperature Tr on the Maxwell table (nodes uniform in s = sqrt(1 - Tr)):
+// the cell's node j and the offset t from it, clamped so that nodes j - 1 .. j + 2 exist whatever
+// Tr is.  False outside [kLatentTmin, kLatentTmax), where there is no band.
+__device__ __forceinline__ bool band_cell(double Tr, double s0, double inv_ds, int& j, double& t)
+{
+    const double d = sqrt(1.0 - Tr) - s0;
+    j = (int)(d * inv_ds);
+    j = j < 1 ? 1 : (j > kMaxwellPoints - 3 ? kMaxwellPoints - 3 : j);
+    t = fma(inv_ds, d, -double(j));
+    return Tr >= kLatentTmin && Tr < kLatentTmax;
+}
+
+// Coexistence densities (rho_1, rho_2) at offset t from node j, cubic Lagrange interpolation on
+// nodes j - 1 .. j + 2 (q[2i] vapour, q[2i + 1] liquid of node j - 1 + i, reduced densities).
+__device__ __forceinline__ void band_eval(double t, const double* q, double rho_c, double& r1, double& r2)
+{
+    // roundings written out, as in work_conduction
+    const double l0 = -t * (t - 1.0) * (t - 2.0) / 6.0;
+    const double l1 = (t + 1.0) * (t - 1.0) * (t - 2.0) * 0.5;
+    const double l2 = -(t + 1.0) * t * (t - 2.0) * 0.5;
+    const double l3 = (t + 1.0) * t * (t - 1.0) / 6.0;
+    r1 = rho_c * fma(l3, q[6], fma(l2, q[4], fma(l0, q[0], l1 * q[2])));
+    r2 = rho_c * fma(l3, q[7], fma(l2, q[5], fma(l0, q[1], l1 * q[3])));
+}
+
+// Coexistence densities (rho_1, rho_2) of the band at reduced temperature Tr on the FP64 Maxwell
+// table.  Returns false outside [kLatentTmin, kLatentTmax).
 __device__ __forceinline__ bool band_limits(double Tr, const double* __restrict__ tab,
                                             double s0, double inv_ds, double rho_c,
                                             double& r1, double& r2)
 {
     if (!(Tr >= kLatentTmin && Tr < kLatentTmax)) return false;
-    const double pos = (sqrt(1.0 - Tr) - s0) * inv_ds;
-    int j = (int)pos;
-    j = j < 1 ? 1 : (j > kMaxwellPoints - 3 ? kMaxwellPoints - 3 : j);
-    const double t = pos - j;
-    // Lagrange basis on nodes j-1, j, j+1, j+2 at offset t from node j
-    const double l0 = -t * (t - 1.0) * (t - 2.0) / 6.0;
-    const double l1 = (t + 1.0) * (t - 1.0) * (t - 2.0) / 2.0;
-    const double l2 = -(t + 1.0) * t * (t - 2.0) / 2.0;
-    const double l3 = (t + 1.0) * t * (t - 1.0) / 6.0;
-    const double* q = tab + 2 * (j - 1);
-    r1 = rho_c * (l0 * q[0] + l1 * q[2] + l2 * q[4] + l3 * q[6]);
-    r2 = rho_c * (l0 * q[1] + l1 * q[3] + l2 * q[5] + l3 * q[7]);
+    int j;
+    double t;
+    band_cell(Tr, s0, inv_ds, j, t);
+    band_eval(t, tab + 2 * (j - 1), rho_c, r1, r2);
     return true;
 }
 

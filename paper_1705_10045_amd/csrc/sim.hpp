@@ -31,6 +31,10 @@ struct lbm_sim {
     int red_blocks = 1;
     int tile_x = 0, tile_y = 0;
     int variant = 0;                     // tile shape of the fused step (see step_tile)
+    bool launch_set = false;             // lbm_set_launch chose the launch
+    bool split = false;                  // the step runs as two launches (split_kernel.hpp)
+    lbm::StepGeom split_geom;            // tiles and z chunks of their collision launch
+    void* d_split = nullptr;             // their moment scratch
 };
 
 namespace lbm {

@@ -515,7 +515,6 @@ __device__ __forceinline__ void step_tile(TileLds<Q, S, R, TX, TY, STASH>& lds,
         const R rho = R(rho_d), E = R(E_d), T = sT[sc][of];
         const R p = o_p[ZH];
         const R inv_rho = R(1) / rho;
-        const R ux = o_jx[ZH] * inv_rho, uy = o_jy[ZH] * inv_rho, uz = o_jz[ZH] * inv_rho;
         const R* Fo = (ZH > 0) ? fprev : fcur;
 
         // z neighbours of the node; beyond a wall: rho mirrored, u*_z mirrored with the
@@ -546,8 +545,8 @@ __device__ __forceinline__ void step_tile(TileLds<Q, S, R, TX, TY, STASH>& lds,
                                              of, cond_half, flags, ph, aux);
 
         NodeCollision<Q, S, R, WN, NMODE == kMrt> c;
-        c.setup(rho, E, ux, uy, uz, Fo[0], Fo[1], Fo[2], inv_rho, dE, keepN, keepG, omega_E,
-                pseudo);
+        c.setup(rho, E, o_jx[ZH], o_jy[ZH], o_jz[ZH], Fo[0], Fo[1], Fo[2], inv_rho, dE, keepN, keepG,
+                omega_E, pseudo);
         c.mrt_prepare(pk_n, ph);
         if constexpr (RED) {
 #pragma unroll
