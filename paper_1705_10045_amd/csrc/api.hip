@@ -394,6 +394,7 @@ StepGeom plan_geometry(const lbm_params& p, int variant, int chunk_request, int 
     }
     g.chunk = chunk;
     g.nchunks = (p.nz + chunk - 1) / chunk;
+    set_reciprocals(g);
     return g;
 }
 
@@ -438,6 +439,7 @@ StepGeom split_geometry(const lbm_params& p, int cus)
     g.chunk = tiles <= round ? 1 : (tiles <= 8 * round ? 2 : 4);
     if (g.chunk > p.nz) g.chunk = p.nz;
     g.nchunks = (p.nz + g.chunk - 1) / g.chunk;
+    set_reciprocals(g);
     return g;
 }
 

@@ -16,7 +16,16 @@ struct StepGeom {
     int chunk;              // z planes per workgroup
     int nchunks;
     int resident;           // workgroups the GPU holds at once (one round), 0 if unknown
+    double inv_nx, inv_ny, inv_ntx, inv_nty;   // reciprocals for index divisions (set_reciprocals)
 };
+
+inline void set_reciprocals(StepGeom& g)
+{
+    g.inv_nx = 1.0 / g.nx;
+    g.inv_ny = 1.0 / g.ny;
+    g.inv_ntx = 1.0 / g.ntx;
+    g.inv_nty = 1.0 / g.nty;
+}
 
 // Read-only tables and the error word shared by every step launch of a simulation.
 struct StepAux {

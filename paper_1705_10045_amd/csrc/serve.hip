@@ -245,6 +245,7 @@ StepGeom pool_geometry(const lbm_params& p)
     g.chunk = kPoolChunk < p.nz ? kPoolChunk : p.nz;
     g.nchunks = (p.nz + g.chunk - 1) / g.chunk;
     g.resident = 0;
+    set_reciprocals(g);
     return g;
 }
 

@@ -79,15 +79,14 @@ k_split_moments(const S* __restrict__ src, void* __restrict__ scratch, const Ste
     const PopIO<S, kAddrBuf> io(src, nullptr, g.plane, 2 * Q);
     const unsigned nxy = (unsigned)g.pitch * (unsigned)g.ny;
     const SplitFields<R> f(scratch, nxy * (unsigned)g.nz);
-    const unsigned rowid = id / (unsigned)g.nx;
+    const unsigned rowid = div_by(id, g.inv_nx);
     const int x = (int)(id - rowid * (unsigned)g.nx);
-    const int z = (int)(rowid / (unsigned)g.ny);
+    const int z = (int)div_by(rowid, g.inv_ny);
     const int y = (int)(rowid - (unsigned)z * (unsigned)g.ny);
     // wrapped x, y * pitch, z * plane of (node - c) for c = +1, 0, -1 (index 1 - c)
-    const int xs[3] = {x == 0 ? g.nx - 1 : x - 1, x, x == g.nx - 1 ? 0 : x + 1};
-    const int ys[3] = {(y == 0 ? g.ny - 1 : y - 1) * g.pitch, y * g.pitch, (y == g.ny - 1 ? 0 : y + 1) * g.pitch};
-    const unsigned zs[3] = {(unsigned)(z == 0 ? g.nz - 1 : z - 1) * nxy, (unsigned)z * nxy,
-                            (unsigned)(z == g.nz - 1 ? 0 : z + 1) * nxy};
+    const int xs[3] = {wrap_dec(x, g.nx), x, wrap_inc(x, g.nx)};
+    const int ys[3] = {wrap_dec(y, g.ny) * g.pitch, y * g.pitch, wrap_inc(y, g.ny) * g.pitch};
+    const unsigned zs[3] = {(unsigned)wrap_dec(z, g.nz) * nxy, (unsigned)z * nxy, (unsigned)wrap_inc(z, g.nz) * nxy};
     const bool has_walls = EXT != kExtNone && ph.walls != 0;
     const bool bb_lo = has_walls && z == 0, bb_hi = has_walls && z == g.nz - 1;
     const unsigned own = zs[1] + (unsigned)(ys[1] + x);
@@ -171,7 +170,8 @@ k_split_collide(const S* __restrict__ src, S* __restrict__ dst, const void* __re
     const unsigned nxy = (unsigned)g.pitch * (unsigned)g.ny;
     const SplitFields<R> m(const_cast<void*>(scratch), nxy * (unsigned)g.nz);
     const int tid = threadIdx.x;
-    const int tix = lb % g.ntx, tiy = (lb / g.ntx) % g.nty, tiz = lb / (g.ntx * g.nty);
+    const int trow = div_uniform(lb, g.inv_ntx), tiz = div_uniform(trow, g.inv_nty);
+    const int tix = lb - trow * g.ntx, tiy = trow - tiz * g.nty;
     const int x0 = tix * TX, y0 = tiy * TY, z0 = tiz * g.chunk;
     const int z1 = min(z0 + g.chunk, g.nz);
     const bool has_walls = EXT != kExtNone && ph.walls != 0;
@@ -181,9 +181,9 @@ k_split_collide(const S* __restrict__ src, S* __restrict__ dst, const void* __re
     const int tx = tid % TX, ty = tid / TX;
     const int ox = x0 + tx, oy = y0 + ty;
     const bool own_in = ox < g.nx && oy < g.ny;
-    const int gx = wrap_index(ox, g.nx), gy = wrap_index(oy, g.ny);
-    const int xs[3] = {wrap_index(gx - 1, g.nx), gx, wrap_index(gx + 1, g.nx)};
-    const int ys[3] = {wrap_index(gy - 1, g.ny) * g.pitch, gy * g.pitch, wrap_index(gy + 1, g.ny) * g.pitch};
+    const int gx = wrap_near(ox, g.nx), gy = wrap_near(oy, g.ny);
+    const int xs[3] = {wrap_dec(gx, g.nx), gx, wrap_inc(gx, g.nx)};
+    const int ys[3] = {wrap_dec(gy, g.ny) * g.pitch, gy * g.pitch, wrap_inc(gy, g.ny) * g.pitch};
     const unsigned oxy = (unsigned)(ys[1] + gx);
     // byte offsets in a plane of the nodes the pulls come from (index 1 - c)
     unsigned pull_xy[3][3];
@@ -198,7 +198,7 @@ k_split_collide(const S* __restrict__ src, S* __restrict__ dst, const void* __re
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const int s = min(tid + r * NTH, NE - 1);
-        p_xy[r] = (unsigned)(wrap_index(x0 - 2 + s % EX, g.nx) + wrap_index(y0 - 2 + s / EX, g.ny) * g.pitch);
+        p_xy[r] = (unsigned)(wrap_near(x0 - 2 + s % EX, g.nx) + wrap_near(y0 - 2 + s / EX, g.ny) * g.pitch);
     }
     const bool p_two = tid + NTH < NE;
     // face neighbour of the tile: rows below and above, then columns left and right
@@ -207,7 +207,7 @@ k_split_collide(const S* __restrict__ src, S* __restrict__ dst, const void* __re
     int hx, hy;
     if (!hxface) { hx = tid % TX; hy = tid < TX ? -1 : TY; }
     else { const int r = tid - 2 * TX; hx = (r & 1) ? TX : -1; hy = halo ? r >> 1 : 0; }
-    const unsigned h_xy = (unsigned)(wrap_index(x0 + hx, g.nx) + wrap_index(y0 + hy, g.ny) * g.pitch);
+    const unsigned h_xy = (unsigned)(wrap_near(x0 + hx, g.nx) + wrap_near(y0 + hy, g.ny) * g.pitch);
     const unsigned hj_xy = h_xy + (hxface ? 0u : m.nodes);   // j_x on the x faces, j_y on the y faces
     const int he = (hx + 2) + EX * (hy + 2), hf = (hx + 1) + FX * (hy + 1);
 
@@ -222,7 +222,7 @@ k_split_collide(const S* __restrict__ src, S* __restrict__ dst, const void* __re
         for (int q = 0; q < 5; ++q) nsum[q] = 0.0;
     }
 
-    auto zrow = [&](int z) { return (unsigned)wrap_index(z, g.nz) * nxy; };
+    auto zrow = [&](int z) { return (unsigned)wrap_near(z, g.nz) * nxy; };
     auto beyond_wall = [&](int z) { return has_walls && (z < 0 || z >= g.nz); };
 
     struct Own { double rho; R T, p, jx, jy, jz; };

@@ -289,9 +289,8 @@ __device__ __forceinline__ void step_tile(TileLds<Q, S, R, TX, TY, STASH>& lds,
     auto uzring = [](int z) { return (z + 6) % UZ; };         // z >= -6
 
     const int tid = threadIdx.x;
-    const int tix = lb % g.ntx;
-    const int tiy = (lb / g.ntx) % g.nty;
-    const int tiz = lb / (g.ntx * g.nty);
+    const int trow = div_uniform(lb, g.inv_ntx), tiz = div_uniform(trow, g.inv_nty);
+    const int tix = lb - trow * g.ntx, tiy = trow - tiz * g.nty;
     const int x0 = tix * TX, y0 = tiy * TY, z0 = tiz * g.chunk;
     const int z1 = min(z0 + g.chunk, g.nz);
     const int nxy = g.pitch * g.ny;   // elements of one z plane (rows padded to the pitch)
@@ -320,14 +319,14 @@ __device__ __forceinline__ void step_tile(TileLds<Q, S, R, TX, TY, STASH>& lds,
             m_e[r] = ex + EX * ey;
             if (ex >= 1 && ex <= EX - 2 && ey >= 1 && ey <= EY - 2)
                 m_f[r] = (ex - 1) + FX * (ey - 1);
-            const int gx = wrap_index(x0 - 2 + ex, g.nx);
-            const int gy = wrap_index(y0 - 2 + ey, g.ny);
-            m_x[r][0] = wrap_index(gx - 1, g.nx);
+            const int gx = wrap_near(x0 - 2 + ex, g.nx);
+            const int gy = wrap_near(y0 - 2 + ey, g.ny);
+            m_x[r][0] = wrap_dec(gx, g.nx);
             m_x[r][1] = gx;
-            m_x[r][2] = wrap_index(gx + 1, g.nx);
-            m_y[r][0] = wrap_index(gy - 1, g.ny) * g.pitch;
+            m_x[r][2] = wrap_inc(gx, g.nx);
+            m_y[r][0] = wrap_dec(gy, g.ny) * g.pitch;
             m_y[r][1] = gy * g.pitch;
-            m_y[r][2] = wrap_index(gy + 1, g.ny) * g.pitch;
+            m_y[r][2] = wrap_inc(gy, g.ny) * g.pitch;
         }
     }
     int f_e[MF], f_f[MF];
@@ -379,9 +378,10 @@ __device__ __forceinline__ void step_tile(TileLds<Q, S, R, TX, TY, STASH>& lds,
         const bool bb_hi = has_walls && zm == g.nz - 1;
         int zoff[3];
         if constexpr (D == 3) {
-            zoff[0] = wrap_index(zm - 1, g.nz) * nxy;
-            zoff[1] = wrap_index(zm, g.nz) * nxy;
-            zoff[2] = wrap_index(zm + 1, g.nz) * nxy;
+            const int zw = wrap_near(zm, g.nz);
+            zoff[0] = wrap_dec(zw, g.nz) * nxy;
+            zoff[1] = zw * nxy;
+            zoff[2] = wrap_inc(zw, g.nz) * nxy;
         } else {
             zoff[0] = zoff[1] = zoff[2] = 0;
         }
@@ -470,11 +470,12 @@ __device__ __forceinline__ void step_tile(TileLds<Q, S, R, TX, TY, STASH>& lds,
         if constexpr (!WN && (kStash || !WE)) return;
         const bool bb_lo = has_walls && zc == 0;
         const bool bb_hi = has_walls && zc == g.nz - 1;
-        const int zoc = wrap_index(zc, g.nz) * nxy;
+        // zc is a plane of the chunk itself
+        const int zoc = zc * nxy;
         int zpull[3] = {zoc, zoc, zoc};
         if constexpr (D == 3) {
-            zpull[0] = wrap_index(zc - 1, g.nz) * nxy;
-            zpull[2] = wrap_index(zc + 1, g.nz) * nxy;
+            zpull[0] = wrap_dec(zc, g.nz) * nxy;
+            zpull[2] = wrap_inc(zc, g.nz) * nxy;
         }
         int row[3][3];
 #pragma unroll
@@ -509,7 +510,7 @@ __device__ __forceinline__ void step_tile(TileLds<Q, S, R, TX, TY, STASH>& lds,
         constexpr bool WN = decltype(with_n)::value;
         const int sc = ring(zc), scm = ring(zc - 1), scp = ring(zc + 1);
         const int suc = uhring(zc), sucm = uzring(zc - 1), sucp = uzring(zc + 1);
-        const int own = wrap_index(zc, g.nz) * nxy + oy * g.pitch + ox;
+        const int own = zc * nxy + oy * g.pitch + ox;
 
         const double rho_d = o_rho[ZH], E_d = o_E[ZH];
         const R rho = R(rho_d), E = R(E_d), T = sT[sc][of];
