@@ -486,6 +486,63 @@ bool ensure_split(lbm_sim* s)
     return false;
 }
 
+// Region of a launch of `steps` D2Q9 steps on tx x ty tiles (multi_kernel.hpp).
+MultiGeom multi_geometry(const lbm_params& p, int tx, int ty, int steps)
+{
+    MultiGeom m{};
+    m.tx = tx;
+    m.ty = ty;
+    m.steps = steps;
+    m.margin = 3 * steps - 1;
+    m.rx = tx + 2 * m.margin;
+    m.ry = p.ny == 1 ? 1 : ty + 2 * m.margin;
+    m.inv_rx = 1.0 / m.rx;
+    return m;
+}
+
+// Tiles and steps per launch of the D2Q9 boxes that take several steps per launch; steps = 0 for
+// the others.  The tiles have to run in one round, one workgroup per CU (its LDS is up to 129 KB),
+// which boxes up to about 256^2 and rows up to 10^5 nodes do: a second round already costs more
+// than single steps (300^2 FP64: 10.3 us per step against 9.3).  Among those, the tile and the
+// step count of least time per step, a launch taking about 2 us and each of its steps 2.1 us
+// plus 0.21 us per further wavefront of the region (measured over 12 tiles and 1 to 16 steps).
+// FP64 times per step: 1000 nodes 6.2 -> 2.2 us, 128^2 7.2 -> 4.4 us, 256^2 7.9 -> 6.1 us.
+MultiGeom plan_multi(const lbm_params& p, int cus)
+{
+    MultiGeom best{};
+    if (p.lattice != 9 || state_bytes(p) >= (1ull << 32)) return best;
+    const int nodes = multi_nodes();
+    double least = 0.0;
+    for (int steps = 1; steps <= 16; ++steps) {
+        for (int ty = (p.ny + cus - 1) / cus; ty <= p.ny; ++ty) {
+            const long long rows = (p.ny + ty - 1) / ty;
+            // the narrowest tile whose columns fit the round
+            const int cols = (int)(cus / rows) < p.nx ? (int)(cus / rows) : p.nx;
+            const int tx = (p.nx + cols - 1) / cols;
+            const MultiGeom m = multi_geometry(p, tx, ty, steps);
+            if (m.ry > nodes) break;
+            if ((long long)m.rx * m.ry > nodes) continue;
+            const int waves = (m.rx * m.ry + 63) / 64;
+            const double t = (2.0 + steps * (2.1 + 0.21 * (waves - 1))) / steps;
+            if (best.steps == 0 || t < least) {
+                best = m;
+                least = t;
+            }
+        }
+    }
+    return best;
+}
+
+hipError_t enqueue_multi(lbm_sim* s, int steps)
+{
+    const MultiGeom m = multi_geometry(s->p, s->multi.tx, s->multi.ty, steps);
+    StepGeom g = s->geom;
+    g.ntx = (s->p.nx + m.tx - 1) / m.tx;
+    g.nty = (s->p.ny + m.ty - 1) / m.ty;
+    set_reciprocals(g);
+    return launch_multi(s->p.storage_bytes, s->buf[s->cur], s->buf[1 - s->cur], g, m, s->phys, s->aux, s->stream);
+}
+
 lbm_status upload_table(lbm_sim* s)
 {
     const MaxwellTable& t = maxwell_table();
@@ -505,9 +562,13 @@ lbm_status enqueue_steps(lbm_sim* s, int nsteps)
         set_error("simulation is not fully initialised (null device pointer)");
         return LBM_EDEVICE;
     }
-    for (int i = 0; i < nsteps; ++i) {
+    for (int i = 0, taken = 1; i < nsteps; i += taken) {
         hipError_t e;
-        if (s->split) {
+        taken = 1;
+        if (s->multi.steps > 0 && !s->launch_set) {
+            taken = nsteps - i < s->multi.steps ? nsteps - i : s->multi.steps;
+            e = enqueue_multi(s, taken);
+        } else if (s->split) {
             e = launch_split_moments(s->p.storage_bytes, s->buf[s->cur], s->d_split, s->split_geom, s->phys,
                                      s->aux, s->stream);
             if (e == hipSuccess)
@@ -519,7 +580,7 @@ lbm_status enqueue_steps(lbm_sim* s, int nsteps)
         }
         if (e != hipSuccess) return hip_fail(e, "step launch");
         s->cur ^= 1;
-        s->step += 1;
+        s->step += taken;
     }
     return LBM_OK;
 }
@@ -629,6 +690,7 @@ lbm_status lbm_init(const lbm_params* params, const double* rho0, const double* 
     s->red_blocks = reduce_blocks(s->n);
     if (e == hipSuccess) e = hipMalloc((void**)&s->d_partials, sizeof(double) * (5 * s->red_blocks + 8));
     if (e != hipSuccess) { lbm_status r = hip_fail(e, "hipMalloc(state)"); lbm_free(s); return r; }
+    s->multi = plan_multi(s->p, s->cus);
     {
         int tx, ty, per_cu;
         step_tile(s->p.lattice, s->p.storage_bytes, s->variant, tx, ty, per_cu);

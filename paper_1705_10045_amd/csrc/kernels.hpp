@@ -62,6 +62,17 @@ hipError_t launch_split_collide(int storage_bytes, const void* src, void* dst, c
 hipError_t launch_split_collide_totals(int storage_bytes, const void* src, void* dst, const void* scratch,
                                        const StepGeom& g, const Phys& ph, const StepAux& aux, double* out,
                                        hipStream_t st);
+// A launch of several D2Q9 steps at once (multi_kernel.hpp): tiles of tx x ty nodes (StepGeom::ntx,
+// nty of them) with a halo of 3 steps - 1 nodes, a region of rx x ry <= multi_nodes() nodes.
+struct MultiGeom {
+    int tx, ty, steps;
+    int margin;             // 3 * steps - 1
+    int rx, ry;             // tx + 2 margin, ty + 2 margin (1 in a box of one row)
+    double inv_rx;
+};
+int multi_nodes();
+hipError_t launch_multi(int storage_bytes, const void* src, void* dst, const StepGeom& g, const MultiGeom& mg,
+                        const Phys& ph, const StepAux& aux, hipStream_t st);
 // workgroups of one step launch (the entries of aux.partials it writes)
 inline long long step_workgroups(const StepGeom& g) { return (long long)g.ntx * g.nty * g.nchunks; }
 // Row pitch of the population planes: x rows padded to whole 128-byte lines, so that rows of

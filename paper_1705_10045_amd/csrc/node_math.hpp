@@ -55,16 +55,16 @@ __device__ __forceinline__ void eos_phi2(double dr, double dE, const Phys& ph, u
         p = ph.p_c * table_pressure(dr * ph.inv_rho_c, Te * ph.inv_T_c, ph, aux.eos_p, inside);
     else
         p = vdw_pressure(dr, Te, ph);
-    phi2 = dr * kTheta - p;
+    phi2 = fma(dr, kTheta, -p);
     ok = inside && phi2 > 0.0 && dr * ph.inv_rho_c < 3.0 && dr > 0.0 && dE == dE && dE < 1e30;
 }
 
 // Force of section 3 in FP64 (a small difference of Phi^2 values) at index e of a plane of
 // row width W:  F = (1/alpha) sum_k G_k Phi_k (A Phi_k + (1 - 2A) Phi(x)) c_k, summed over
 // pairs of opposite directions.  pm, p0, pp are the Phi planes at z - 1, z, z + 1.
-template <int Q, int W>
+template <int Q>
 __device__ __forceinline__ void force_at(const double* pm, const double* p0, const double* pp,
-                                         int e, double A, double inv_alpha, double& Fx,
+                                         int e, int W, double A, double inv_alpha, double& Fx,
                                          double& Fy, double& Fz)
 {
     using L = Lattice<Q>;
@@ -93,9 +93,9 @@ __device__ __forceinline__ void force_at(const double* pm, const double* p0, con
 // c_V chi (rho_i + rho_j)/2 (sections 4 and 6.2) at index e of planes of row width W.  r0 and t0
 // are the rho and T planes of the node; rm, tm and rp, tp the values of its neighbours at z - 1
 // and z + 1 (D = 3).
-template <int D, class R, int W>
+template <int D, class R>
 __device__ __forceinline__ R work_conduction(R p, R div, R rho, R rm, const R* r0, R rp, R tm, const R* t0,
-                                             R tp, int e, R cond_half, unsigned flags)
+                                             R tp, int e, int W, R cond_half, unsigned flags)
 {
     // the contractions are written out: every launch form has to round them alike
     R dE = R(0);
@@ -128,12 +128,12 @@ __device__ __forceinline__ void latent_term(R& dE, double r1, double r2, R rho, 
 
 // Energy source dE of sections 4-6: work, conduction (see work_conduction) and the latent-heat
 // term inside the coexistence band.
-template <int D, class R, int W, bool TABLE = false>
+template <int D, class R, bool TABLE = false>
 __device__ __forceinline__ R energy_source(R p, R div, R rho, R T, R rm, const R* r0, R rp,
-                                           R tm, const R* t0, R tp, int e, R cond_half,
+                                           R tm, const R* t0, R tp, int e, int W, R cond_half,
                                            unsigned flags, const Phys& ph, const StepAux& aux)
 {
-    R dE = work_conduction<D, R, W>(p, div, rho, rm, r0, rp, tm, t0, tp, e, cond_half, flags);
+    R dE = work_conduction<D, R>(p, div, rho, rm, r0, rp, tm, t0, tp, e, W, cond_half, flags);
     if (flags & kLatent) {
         const double Te = (flags & kBaro) ? ph.T0_baro : double(T);
         double r1, r2;
@@ -240,7 +240,7 @@ __device__ __forceinline__ R dot_c(int k, R x, R y, R z, F last)
 // FP64 over the values actually stored (the BGK, EDM and pseudoforce increments sum to zero and
 // dg(1) sums to dE), so rounding of the lattice weights cannot create mass or energy.
 // With MRT (which re-reads N_k like any tau != 1) the moving N'_k also lose
-// sum_i am_i M_ik over the rows of MrtRows, am_i = (s_i - omega) m_i / |M_i|^2 with m_i the
+// sum_i am_i M_ik / |M_i|^2 over the rows of MrtRows, am_i = (s_i - omega) m_i with m_i the
 // row's moment of N - rho P(u); those terms sum to zero over k, so the rest population still
 // closes the mass balance.
 template <int Q, class S, class R, bool WN, bool MRT = false>
@@ -304,7 +304,7 @@ struct NodeCollision {
             for (int k = 1; k < Q; ++k) {
                 const R w = R(weight<Q>(k));
                 const R cu = dot_u(k);
-                const R P = fma(R(4.5) * w, cu * cu, w * base_u) + R(3) * w * cu;
+                const R P = fma(R(3) * w, cu, fma(R(4.5) * w, cu * cu, w * base_u));
                 const R f = fma(-rho, P, pk_n[k]);
 #pragma unroll
                 for (int i = 0; i < G::N; ++i) {
@@ -315,7 +315,7 @@ struct NodeCollision {
             const R d[4] = {R(ph.mrt_de), R(ph.mrt_deps), R(ph.mrt_dq), R(ph.mrt_dm)};
 #pragma unroll
             for (int i = 0; i < G::N; ++i)
-                am[i] = d[mrt_group(G::id[i])] * m[i] * R(1.0 / mrt_norm2<Q>(G::id[i]));
+                am[i] = d[mrt_group(G::id[i])] * m[i];
         }
     }
 
@@ -327,9 +327,9 @@ struct NodeCollision {
         const R w = R(weight<Q>(k));
         const R cu = dot_u(k);
         const R cv = dot_v(k);
-        const R eu = fma(R(4.5) * w, cu * cu, w * base_u), ou = R(3) * w * cu;
-        const R ev = fma(R(4.5) * w, cv * cv, w * base_v), ov = R(3) * w * cv;
-        const R Pu[2] = {eu + ou, eu - ou}, Pv[2] = {ev + ov, ev - ov};
+        const R eu = fma(R(4.5) * w, cu * cu, w * base_u), ev = fma(R(4.5) * w, cv * cv, w * base_v);
+        const R w3 = R(3) * w;
+        const R Pu[2] = {fma(w3, cu, eu), fma(-w3, cu, eu)}, Pv[2] = {fma(w3, cv, ev), fma(-w3, cv, ev)};
         const int kk[2] = {k, ko};
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -339,13 +339,19 @@ struct NodeCollision {
             if constexpr (MRT) {
 #pragma unroll
                 for (int i = 0; i < NG; ++i) {
+                    // unit entries take the product with 1/|M|^2 unrounded
                     const double coef = mrt_row<Q>(MrtRows<Q>::id[i], q);
-                    if (coef != 0.0) nn = fma(R(-coef), am[i], nn);
+                    const R inv = R(1.0 / mrt_norm2<Q>(MrtRows<Q>::id[i]));
+                    if (coef == 1.0) nn = fma(-am[i], inv, nn);
+                    else if (coef == -1.0) nn = fma(am[i], inv, nn);
+                    else if (coef != 0.0) nn = fma(R(-coef), am[i] * inv, nn);
                 }
             }
             const R gn = fma(gK, pk_e[q], fma(gU, Pu[h], gV * Pv[h]));
             const S nn_s = S(nn), gn_s = S(gn);
-            sumN += double(nn_s);
+            // (FP64 with tau = 1: the product enters the sum unrounded)
+            if constexpr (!WN && sizeof(S) == 8) sumN = fma(double(rho), double(Pv[h]), sumN);
+            else sumN += double(nn_s);
             sumG += double(gn_s);
             out[2 * h] = nn_s;
             out[2 * h + 1] = gn_s;

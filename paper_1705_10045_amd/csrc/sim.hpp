@@ -35,6 +35,7 @@ struct lbm_sim {
     bool split = false;                  // the step runs as two launches (split_kernel.hpp)
     lbm::StepGeom split_geom;            // tiles and z chunks of their collision launch
     void* d_split = nullptr;             // their moment scratch
+    lbm::MultiGeom multi{};              // D2Q9: steps taken per launch (0: single steps) and their tiles
 };
 
 namespace lbm {

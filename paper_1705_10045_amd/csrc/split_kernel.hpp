@@ -291,11 +291,11 @@ k_split_collide(const S* __restrict__ src, S* __restrict__ dst, const void* __re
         const double* pp = (has_walls && zf == g.nz - 1) ? p0 : lds.phi[(zf + 1) & (RING - 1)];
         auto force = [&](int e, double rf, R& ax, R& ay, R& az) {
             double fx, fy, fz;
-            force_at<Q, EX>(pm, p0, pp, e, ph.A, ph.inv_alpha, fx, fy, fz);
+            force_at<Q>(pm, p0, pp, e, EX, ph.A, ph.inv_alpha, fx, fy, fz);
             if (has_g) {
-                fx += rf * ph.g[0];
-                fy += rf * ph.g[1];
-                fz += rf * ph.g[2];
+                fx = fma(rf, ph.g[0], fx);
+                fy = fma(rf, ph.g[1], fy);
+                fz = fma(rf, ph.g[2], fz);
             }
             ax = R(fx); ay = R(fy); az = R(fz);
         };
@@ -399,11 +399,11 @@ k_split_collide(const S* __restrict__ src, S* __restrict__ dst, const void* __re
         div += R(0.5) * (uzp - uzm);
         R dE;
         if constexpr (EXT == kExtTable) {
-            dE = energy_source<3, R, FX, true>(p, div, rho, T, rzm, lds.rho[b], rzp, tzm, lds.T[b], tzp, of,
-                                               cond_half, flags, ph, aux);
+            dE = energy_source<3, R, true>(p, div, rho, T, rzm, lds.rho[b], rzp, tzm, lds.T[b], tzp, of, FX,
+                                           cond_half, flags, ph, aux);
         } else {
-            dE = work_conduction<3, R, FX>(p, div, rho, rzm, lds.rho[b], rzp, tzm, lds.T[b], tzp, of, cond_half,
-                                           flags);
+            dE = work_conduction<3, R>(p, div, rho, rzm, lds.rho[b], rzp, tzm, lds.T[b], tzp, of, FX, cond_half,
+                                       flags);
             if (flags & kLatent) {
                 double r1, r2;
                 band_eval(tcell, q, ph.rho_c, r1, r2);

@@ -542,8 +542,8 @@ __device__ __forceinline__ void step_tile(TileLds<Q, S, R, TX, TY, STASH>& lds,
         R div = R(0.5) * (sUh[0][suc][of + 1] - sUh[0][suc][of - 1]) +
                 R(0.5) * (sUh[1][suc][of + FX] - sUh[1][suc][of - FX]);
         if constexpr (D == 3) div += R(0.5) * (uzp - uzm);
-        const R dE = energy_source<D, R, FX, kTable>(p, div, rho, T, rzm, sRho[sc], rzp, tzm, sT[sc], tzp,
-                                             of, cond_half, flags, ph, aux);
+        const R dE = energy_source<D, R, kTable>(p, div, rho, T, rzm, sRho[sc], rzp, tzm, sT[sc], tzp,
+                                         of, FX, cond_half, flags, ph, aux);
 
         NodeCollision<Q, S, R, WN, NMODE == kMrt> c;
         c.setup(rho, E, o_jx[ZH], o_jy[ZH], o_jz[ZH], Fo[0], Fo[1], Fo[2], inv_rho, dE, keepN, keepG,
@@ -657,12 +657,12 @@ __device__ __forceinline__ void step_tile(TileLds<Q, S, R, TX, TY, STASH>& lds,
                 const int e = f_e[r];
                 const int f = f_f[r];
                 double fx, fy, fz;
-                force_at<Q, EX>(pm, sPhi[spf], pp, e, ph.A, ph.inv_alpha, fx, fy, fz);
+                force_at<Q>(pm, sPhi[spf], pp, e, EX, ph.A, ph.inv_alpha, fx, fy, fz);
                 if (has_g) {   // body force rho g (eq:edm takes any force)
                     const double rf = double(sRho[sf][f]);
-                    fx += rf * ph.g[0];
-                    fy += rf * ph.g[1];
-                    fz += rf * ph.g[2];
+                    fx = fma(rf, ph.g[0], fx);
+                    fy = fma(rf, ph.g[1], fy);
+                    fz = fma(rf, ph.g[2], fz);
                 }
                 const R Fx = R(fx), Fy = R(fy), Fz = R(fz);
                 const R inv_rho = R(1) / sRho[sf][f];
