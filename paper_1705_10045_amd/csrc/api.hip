@@ -838,14 +838,15 @@ lbm_status lbm_moments(lbm_sim* s, double* rho, double* u_star, double* E, doubl
     if (st != LBM_OK) return st;
     const long long n = s->n;
     double* scr = s->d_scratch;
-    double* d_us = scr + 7 * n;
+    // behind the two fields of the moment kernels' own scratch
+    double *d_rho = scr + 2 * n, *d_us = scr + 3 * n, *d_E = scr + 6 * n, *d_T = scr + 7 * n;
     hipError_t e = launch_moments(s->p.lattice, s->p.storage_bytes, s->buf[s->cur], scr, s->p.nx, s->p.ny,
-                                  s->p.nz, s->geom.pitch, s->plane, s->phys, s->aux.eos_p, s->d_err, nullptr,
-                                  u_star ? d_us : nullptr, nullptr, nullptr, s->stream);
-    if (e == hipSuccess && rho) e = hipMemcpyAsync(rho, scr, sizeof(double) * n, hipMemcpyDeviceToHost, s->stream);
+                                  s->p.nz, s->geom.pitch, s->plane, s->phys, s->aux.eos_p, s->d_err, rho ? d_rho : nullptr,
+                                  u_star ? d_us : nullptr, E ? d_E : nullptr, T ? d_T : nullptr, s->stream);
+    if (e == hipSuccess && rho) e = hipMemcpyAsync(rho, d_rho, sizeof(double) * n, hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess && u_star) e = hipMemcpyAsync(u_star, d_us, sizeof(double) * 3 * n, hipMemcpyDeviceToHost, s->stream);
-    if (e == hipSuccess && E) e = hipMemcpyAsync(E, scr + 4 * n, sizeof(double) * n, hipMemcpyDeviceToHost, s->stream);
-    if (e == hipSuccess && T) e = hipMemcpyAsync(T, scr + 5 * n, sizeof(double) * n, hipMemcpyDeviceToHost, s->stream);
+    if (e == hipSuccess && E) e = hipMemcpyAsync(E, d_E, sizeof(double) * n, hipMemcpyDeviceToHost, s->stream);
+    if (e == hipSuccess && T) e = hipMemcpyAsync(T, d_T, sizeof(double) * n, hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return hip_fail(e, "moments");
     return read_error_word(s);

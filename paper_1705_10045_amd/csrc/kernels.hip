@@ -12,141 +12,165 @@ using step_launch::launch_step_t;
 
 namespace {
 
-__device__ __forceinline__ void node_xyz(long long i, int nx, int ny, int& x, int& y, int& z)
+// Node of thread `id` (x fastest) of a box, and its neighbours' coordinates on the periodic axes.
+// The extents' reciprocals come from the host: three integer remainders per direction, in 64 bits,
+// took the moment kernels as long as their memory traffic.
+struct BoxIndex {
+    int nx, ny, nz, pitch;
+    double inv_nx, inv_ny;
+};
+
+BoxIndex box_index(int nx, int ny, int nz, int pitch)
 {
-    x = (int)(i % nx);
-    const long long r = i / nx;
-    y = (int)(r % ny);
-    z = (int)(r / ny);
+    return BoxIndex{nx, ny, nz, pitch, 1.0 / nx, 1.0 / ny};
 }
 
-__device__ __forceinline__ long long node_index(int x, int y, int z, int nx, int ny, int nz)
-{
-    return wrap_index(x, nx) + (long long)nx * (wrap_index(y, ny) + (long long)ny * wrap_index(z, nz));
-}
-
-// Element of node (x, y, z) (periodic wrap) in a population plane whose rows have the pitch.
-__device__ __forceinline__ long long buf_index(int x, int y, int z, int nx, int ny, int nz, int pitch)
-{
-    return wrap_index(x, nx) + (long long)pitch * (wrap_index(y, ny) + (long long)ny * wrap_index(z, nz));
-}
+struct NodeIndex {
+    int x[3], y[3], z[3];   // coordinate - 1, itself, + 1, wrapped
+    __device__ __forceinline__ NodeIndex(unsigned id, const BoxIndex& b)
+    {
+        const unsigned row = div_by(id, b.inv_nx), zz = div_by(row, b.inv_ny);
+        x[1] = (int)(id - row * (unsigned)b.nx);
+        y[1] = (int)(row - zz * (unsigned)b.ny);
+        z[1] = (int)zz;
+        x[0] = wrap_dec(x[1], b.nx); x[2] = wrap_inc(x[1], b.nx);
+        y[0] = wrap_dec(y[1], b.ny); y[2] = wrap_inc(y[1], b.ny);
+        z[0] = wrap_dec(z[1], b.nz); z[2] = wrap_inc(z[1], b.nz);
+    }
+    // element of the node displaced by (dx, dy, dz) in a field with rows of the given length
+    __device__ __forceinline__ unsigned at(int dx, int dy, int dz, int row, int ny) const
+    {
+        return (unsigned)x[1 + dx] + (unsigned)row * ((unsigned)y[1 + dy] + (unsigned)ny * (unsigned)z[1 + dz]);
+    }
+};
 
 // Equilibrium initial state N_k = rho0 P_k(u0), g_k = rho0 c_v T0 P_k(u0) (eq:feq, section 4),
-// stored in pull form: node y keeps, for direction k, the value belonging to node y + c_k.
+// stored in pull form: node y keeps, for direction k, the value belonging to node y + c_k.  Each
+// node reads its five fields once and scatters (gathering them from the 18 neighbours took twice
+// as long).
 template <int Q, class S>
 __global__ void k_init(S* __restrict__ buf, const double* __restrict__ rho0,
-                       const double* __restrict__ u0, const double* __restrict__ T0, int nx,
-                       int ny, int nz, int pitch, long long plane, double c_v, int walls)
+                       const double* __restrict__ u0, const double* __restrict__ T0, const BoxIndex box,
+                       long long plane, double c_v, int walls)
 {
     using L = Lattice<Q>;
-    const long long n = (long long)nx * ny * nz;
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const unsigned n = (unsigned)box.nx * (unsigned)box.ny * (unsigned)box.nz;
+    const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    int x, y, z;
-    node_xyz(i, nx, ny, x, y, z);
-    const long long b = buf_index(x, y, z, nx, ny, nz, pitch);
+    const NodeIndex node(i, box);
+    const int z = node.z[1];
+    const unsigned own = node.at(0, 0, 0, box.pitch, box.ny);
+    const double rho = rho0[i];
+    const double ux = u0[i], uy = u0[(long long)n + i], uz = u0[2 * (long long)n + i];
+    const double E = rho * c_v * T0[i];
+    const double uu = ux * ux + uy * uy + uz * uz;
+    // the node scatters its own equilibrium: direction k of it is stored at the node it is pulled
+    // from, or, where that is beyond a wall, at the node itself as the opposite direction
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
-        // population k stored at node i is pulled by node i + c_k; toward a wall, it is pulled
-        // back by node i itself as the opposite direction
-        long long j = node_index(x + L::cx[k], y + L::cy[k], z + L::cz[k], nx, ny, nz);
-        int kd = k;
-        if (walls && (z + L::cz[k] < 0 || z + L::cz[k] >= nz)) {
-            j = i;
-            kd = opposite<Q>(k);
-        }
-        const double rho = rho0[j];
-        const double ux = u0[j], uy = u0[n + j], uz = u0[2 * n + j];
-        const double E = rho * c_v * T0[j];
-        const double cu = L::cx[kd] * ux + L::cy[kd] * uy + L::cz[kd] * uz;
-        const double P = eq_poly(weight<Q>(kd), cu, ux * ux + uy * uy + uz * uz);
-        buf[(long long)k * plane + b] = S(rho * P);
-        buf[(long long)(Q + k) * plane + b] = S(E * P);
+        const bool bounced = walls && (z - L::cz[k] < 0 || z - L::cz[k] >= box.nz);
+        const int kd = bounced ? opposite<Q>(k) : k;
+        const unsigned b = bounced ? own : node.at(-L::cx[k], -L::cy[k], -L::cz[k], box.pitch, box.ny);
+        const double cu = L::cx[k] * ux + L::cy[k] * uy + L::cz[k] * uz;
+        const double P = eq_poly(weight<Q>(k), cu, uu);
+        buf[(long long)kd * plane + b] = S(rho * P);
+        buf[(long long)(Q + kd) * plane + b] = S(E * P);
     }
 }
 
-// Moments of the current state in FP64: scratch = [rho | jx | jy | jz | E | T | Phi].
+// Moments of the current state in FP64, one node per thread: rho, E and T where an output is
+// given; for u*, rho and Phi into the scratch and j into the u* output itself, which the second
+// kernel turns into u* in place.  Bound by its traffic (152 bytes read and 56 written per FP32
+// D3Q19 node; 5.2 TB/s at 128^3).
+struct MomentOut {
+    double *rho, *us, *E, *T;       // any may be null
+    double *rho_tmp, *phi;          // used with us
+};
+
 template <int Q, class S>
-__global__ void k_moments_a(const S* __restrict__ buf, double* __restrict__ scr, int nx, int ny,
-                            int nz, int pitch, long long plane, Phys ph,
-                            const double* __restrict__ eos_p, int* err)
+__global__ void k_moments_a(const S* __restrict__ buf, const MomentOut out, const BoxIndex box,
+                            long long plane, Phys ph, const double* __restrict__ eos_p, int* err)
 {
     using L = Lattice<Q>;
-    const long long n = (long long)nx * ny * nz;
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const unsigned n = (unsigned)box.nx * (unsigned)box.ny * (unsigned)box.nz;
+    const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    int x, y, z;
-    node_xyz(i, nx, ny, x, y, z);
+    const NodeIndex node(i, box);
+    const int z = node.z[1];
+    const unsigned own = node.at(0, 0, 0, box.pitch, box.ny);
     double rho = 0, jx = 0, jy = 0, jz = 0, E = 0;
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
-        long long j = buf_index(x - L::cx[k], y - L::cy[k], z - L::cz[k], nx, ny, nz, pitch);
-        int pk = k;
-        if (ph.walls && (z - L::cz[k] < 0 || z - L::cz[k] >= nz)) {   // bounce-back at a wall
-            pk = opposite<Q>(k);
-            j = buf_index(x, y, z, nx, ny, nz, pitch);
+        unsigned j = node.at(-L::cx[k], -L::cy[k], -L::cz[k], box.pitch, box.ny);
+        long long pk = (long long)k * plane;
+        if (L::cz[k] != 0 && ph.walls && (z - L::cz[k] < 0 || z - L::cz[k] >= box.nz)) {   // bounce-back at a wall
+            pk = (long long)opposite<Q>(k) * plane;
+            j = own;
         }
-        const double nk = double(buf[(long long)pk * plane + j]);
+        const double nk = double(buf[pk + j]);
         rho += nk;
-        jx += L::cx[k] * nk;
-        jy += L::cy[k] * nk;
-        jz += L::cz[k] * nk;
-        E += double(buf[(long long)(Q + pk) * plane + j]);
+        if (L::cx[k]) jx += L::cx[k] * nk;
+        if (L::cy[k]) jy += L::cy[k] * nk;
+        if (L::cz[k]) jz += L::cz[k] * nk;
+        E += double(buf[(long long)Q * plane + pk + j]);
     }
     const double T = E / (rho * ph.c_v);
     const double Te = (ph.flags & kBaro) ? ph.T0_baro : T;
     bool inside = true;
     const double p = ph.eos ? ph.p_c * table_pressure(rho * ph.inv_rho_c, Te * ph.inv_T_c, ph, eos_p, inside)
                             : vdw_pressure(rho, Te, ph);
-    double phi2 = rho * kTheta - p;
+    double phi2 = fma(rho, kTheta, -p);
     if (!inside || !(phi2 > 0.0) || !(rho * ph.inv_rho_c < 3.0) || !(rho > 0.0) || !(E == E)) {
         atomicOr(err, 1);
         phi2 = 0.0;
     }
-    scr[i] = rho;
-    scr[n + i] = jx;
-    scr[2 * n + i] = jy;
-    scr[3 * n + i] = jz;
-    scr[4 * n + i] = E;
-    scr[5 * n + i] = T;
-    scr[6 * n + i] = sqrt(phi2);
+    if (out.rho) out.rho[i] = rho;
+    if (out.E) out.E[i] = E;
+    if (out.T) out.T[i] = T;
+    if (out.us) {
+        if (!out.rho) out.rho_tmp[i] = rho;
+        out.phi[i] = sqrt(phi2);
+        out.us[i] = jx;
+        out.us[(long long)n + i] = jy;
+        out.us[2 * (long long)n + i] = jz;
+    }
 }
 
-// u* = (j + F/2)/rho (eq:ustar) with the force of section 3 from the Phi field (mirrored beyond
-// walls) plus the body force rho g; writes the requested output fields (any pointer may be
-// null).
+// u* = (j + F/2)/rho (eq:ustar) in place of j, with the force of section 3 from the Phi field
+// (mirrored beyond walls) plus the body force rho g.
 template <int Q>
-__global__ void k_moments_b(const double* __restrict__ scr, int nx, int ny, int nz, Phys ph,
-                            double* __restrict__ rho_o, double* __restrict__ us_o,
-                            double* __restrict__ E_o, double* __restrict__ T_o)
+__global__ void k_moments_b(const MomentOut out, const BoxIndex box, Phys ph)
 {
     using L = Lattice<Q>;
-    const long long n = (long long)nx * ny * nz;
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const unsigned n = (unsigned)box.nx * (unsigned)box.ny * (unsigned)box.nz;
+    const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    int x, y, z;
-    node_xyz(i, nx, ny, x, y, z);
-    const double* Phi = scr + 6 * n;
+    NodeIndex node(i, box);
+    if (ph.walls) {
+        if (node.z[1] == 0) node.z[0] = 0;
+        if (node.z[1] == box.nz - 1) node.z[2] = box.nz - 1;
+    }
+    const double* __restrict__ Phi = out.phi;
     double s1[3] = {0, 0, 0}, s2[3] = {0, 0, 0};
 #pragma unroll
     for (int k = 1; k < Q; ++k) {
-        int zz = z + L::cz[k];
-        if (ph.walls) zz = zz < 0 ? -1 - zz : (zz >= nz ? 2 * nz - 1 - zz : zz);
-        const double p = Phi[node_index(x + L::cx[k], y + L::cy[k], zz, nx, ny, nz)];
+        const double p = Phi[node.at(L::cx[k], L::cy[k], L::cz[k], box.nx, box.ny)];
         const double G = force_coef<Q>(k);
-        s1[0] += G * p * p * L::cx[k]; s1[1] += G * p * p * L::cy[k]; s1[2] += G * p * p * L::cz[k];
-        s2[0] += G * p * L::cx[k]; s2[1] += G * p * L::cy[k]; s2[2] += G * p * L::cz[k];
-    }
-    const double rho = scr[i];
-    if (rho_o) rho_o[i] = rho;
-    if (E_o) E_o[i] = scr[4 * n + i];
-    if (T_o) T_o[i] = scr[5 * n + i];
-    if (us_o) {
+        const int c[3] = {L::cx[k], L::cy[k], L::cz[k]};
+#pragma unroll
         for (int a = 0; a < 3; ++a) {
-            const double F = (ph.A * s1[a] + (1.0 - 2.0 * ph.A) * Phi[i] * s2[a]) * ph.inv_alpha +
-                             rho * ph.g[a];
-            us_o[a * n + i] = (scr[(1 + a) * n + i] + 0.5 * F) / rho;
+            if (c[a] == 0) continue;
+            s1[a] += G * p * p * c[a];
+            s2[a] += G * p * c[a];
         }
+    }
+    const double rho = out.rho ? out.rho[i] : out.rho_tmp[i];
+    const double phi = Phi[i];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double F = (ph.A * s1[a] + (1.0 - 2.0 * ph.A) * phi * s2[a]) * ph.inv_alpha + rho * ph.g[a];
+        double* u = out.us + (long long)a * n + i;
+        *u = (*u + 0.5 * F) / rho;
     }
 }
 
@@ -337,10 +361,11 @@ hipError_t launch_init(int Q, int storage_bytes, void* buf, const double* rho0, 
 {
     const long long n = (long long)nx * ny * nz;
     const dim3 grid(blocks_for(n, 256)), block(256);
-    if (Q == 19 && storage_bytes == 4) hipLaunchKernelGGL((k_init<19, float>), grid, block, 0, st, (float*)buf, rho0, u0, T0, nx, ny, nz, pitch, plane, c_v, walls);
-    else if (Q == 19 && storage_bytes == 8) hipLaunchKernelGGL((k_init<19, double>), grid, block, 0, st, (double*)buf, rho0, u0, T0, nx, ny, nz, pitch, plane, c_v, walls);
-    else if (Q == 9 && storage_bytes == 4) hipLaunchKernelGGL((k_init<9, float>), grid, block, 0, st, (float*)buf, rho0, u0, T0, nx, ny, nz, pitch, plane, c_v, 0);
-    else if (Q == 9 && storage_bytes == 8) hipLaunchKernelGGL((k_init<9, double>), grid, block, 0, st, (double*)buf, rho0, u0, T0, nx, ny, nz, pitch, plane, c_v, 0);
+    const BoxIndex box = box_index(nx, ny, nz, pitch);
+    if (Q == 19 && storage_bytes == 4) hipLaunchKernelGGL((k_init<19, float>), grid, block, 0, st, (float*)buf, rho0, u0, T0, box, plane, c_v, walls);
+    else if (Q == 19 && storage_bytes == 8) hipLaunchKernelGGL((k_init<19, double>), grid, block, 0, st, (double*)buf, rho0, u0, T0, box, plane, c_v, walls);
+    else if (Q == 9 && storage_bytes == 4) hipLaunchKernelGGL((k_init<9, float>), grid, block, 0, st, (float*)buf, rho0, u0, T0, box, plane, c_v, 0);
+    else if (Q == 9 && storage_bytes == 8) hipLaunchKernelGGL((k_init<9, double>), grid, block, 0, st, (double*)buf, rho0, u0, T0, box, plane, c_v, 0);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
@@ -351,13 +376,17 @@ hipError_t launch_moments(int Q, int storage_bytes, const void* buf, double* scr
 {
     const long long n = (long long)nx * ny * nz;
     const dim3 grid(blocks_for(n, 256)), block(256);
-    if (Q == 19 && storage_bytes == 4) hipLaunchKernelGGL((k_moments_a<19, float>), grid, block, 0, st, (const float*)buf, scratch, nx, ny, nz, pitch, plane, ph, eos_p, err);
-    else if (Q == 19 && storage_bytes == 8) hipLaunchKernelGGL((k_moments_a<19, double>), grid, block, 0, st, (const double*)buf, scratch, nx, ny, nz, pitch, plane, ph, eos_p, err);
-    else if (Q == 9 && storage_bytes == 4) hipLaunchKernelGGL((k_moments_a<9, float>), grid, block, 0, st, (const float*)buf, scratch, nx, ny, nz, pitch, plane, ph, eos_p, err);
-    else if (Q == 9 && storage_bytes == 8) hipLaunchKernelGGL((k_moments_a<9, double>), grid, block, 0, st, (const double*)buf, scratch, nx, ny, nz, pitch, plane, ph, eos_p, err);
+    const BoxIndex box = box_index(nx, ny, nz, pitch);
+    const MomentOut out{rho, us, E, T, scratch, scratch + n};
+    if (Q == 19 && storage_bytes == 4) hipLaunchKernelGGL((k_moments_a<19, float>), grid, block, 0, st, (const float*)buf, out, box, plane, ph, eos_p, err);
+    else if (Q == 19 && storage_bytes == 8) hipLaunchKernelGGL((k_moments_a<19, double>), grid, block, 0, st, (const double*)buf, out, box, plane, ph, eos_p, err);
+    else if (Q == 9 && storage_bytes == 4) hipLaunchKernelGGL((k_moments_a<9, float>), grid, block, 0, st, (const float*)buf, out, box, plane, ph, eos_p, err);
+    else if (Q == 9 && storage_bytes == 8) hipLaunchKernelGGL((k_moments_a<9, double>), grid, block, 0, st, (const double*)buf, out, box, plane, ph, eos_p, err);
     else return hipErrorInvalidValue;
-    if (Q == 19) hipLaunchKernelGGL((k_moments_b<19>), grid, block, 0, st, scratch, nx, ny, nz, ph, rho, us, E, T);
-    else hipLaunchKernelGGL((k_moments_b<9>), grid, block, 0, st, scratch, nx, ny, nz, ph, rho, us, E, T);
+    if (us) {
+        if (Q == 19) hipLaunchKernelGGL((k_moments_b<19>), grid, block, 0, st, out, box, ph);
+        else hipLaunchKernelGGL((k_moments_b<9>), grid, block, 0, st, out, box, ph);
+    }
     return hipGetLastError();
 }
 

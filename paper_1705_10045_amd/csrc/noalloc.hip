@@ -18,7 +18,7 @@ namespace lbm {
 namespace {
 
 constexpr size_t kStaticScratchBytes = size_t(128) << 20;
-// the moment kernels keep rho, j, E, T and Phi: 7 doubles per node
+// 7 doubles per node (the moment kernels use two of them, for rho and Phi)
 constexpr long long kNoallocMaxNodes = (long long)(kStaticScratchBytes / (7 * sizeof(double)));
 
 static __device__ __align__(256) double scratch[kStaticScratchBytes / sizeof(double)];

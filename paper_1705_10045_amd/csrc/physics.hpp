@@ -142,14 +142,9 @@ __device__ __forceinline__ bool band_limits(double Tr, const double* __restrict_
     return true;
 }
 
-__host__ __device__ inline int wrap_index(int i, int n)
-{
-    int r = i % n;
-    return r < 0 ? r + n : r;
-}
-
-// The same by steps of n: no step or one wherever the box is as wide as a tile and its halo, where
-// an integer remainder is some 25 vector instructions, also for uniform operands.
+// Coordinate i on a periodic axis of n nodes, by steps of n: no step or one wherever the box is as
+// wide as a tile and its halo, where an integer remainder is some 25 vector instructions, also for
+// uniform operands.
 __device__ __forceinline__ int wrap_near(int i, int n)
 {
     i += i < 0 ? n : 0;

@@ -579,16 +579,16 @@ lbm_status lbm_pool_collect(lbm_pool* p, long long ticket, double* rho, double* 
     if (lbm_status sd = use_device(p->device); sd != LBM_OK) return sd;
     const long long n = (long long)ps.params.nx * ps.params.ny * ps.params.nz;
     double* scr = p->d_scratch;
-    double* d_us = scr + 7 * n;
+    double *d_rho = scr + 2 * n, *d_us = scr + 3 * n, *d_E = scr + 6 * n, *d_T = scr + 7 * n;
     int* d_err = p->d_errs + s;
     // on the side stream: the slot has finished, so a replay in flight does not advance it
     hipError_t e = launch_moments(19, 4, d.buf[d.parity], scr, ps.params.nx, ps.params.ny, ps.params.nz,
-                                  d.geom.pitch, d.geom.plane, d.phys, d.eos_p, d_err, nullptr,
-                                  u_star ? d_us : nullptr, nullptr, nullptr, p->side);
-    if (e == hipSuccess && rho) e = hipMemcpyAsync(rho, scr, sizeof(double) * n, hipMemcpyDeviceToHost, p->side);
+                                  d.geom.pitch, d.geom.plane, d.phys, d.eos_p, d_err, rho ? d_rho : nullptr,
+                                  u_star ? d_us : nullptr, E ? d_E : nullptr, T ? d_T : nullptr, p->side);
+    if (e == hipSuccess && rho) e = hipMemcpyAsync(rho, d_rho, sizeof(double) * n, hipMemcpyDeviceToHost, p->side);
     if (e == hipSuccess && u_star) e = hipMemcpyAsync(u_star, d_us, sizeof(double) * 3 * n, hipMemcpyDeviceToHost, p->side);
-    if (e == hipSuccess && E) e = hipMemcpyAsync(E, scr + 4 * n, sizeof(double) * n, hipMemcpyDeviceToHost, p->side);
-    if (e == hipSuccess && T) e = hipMemcpyAsync(T, scr + 5 * n, sizeof(double) * n, hipMemcpyDeviceToHost, p->side);
+    if (e == hipSuccess && E) e = hipMemcpyAsync(E, d_E, sizeof(double) * n, hipMemcpyDeviceToHost, p->side);
+    if (e == hipSuccess && T) e = hipMemcpyAsync(T, d_T, sizeof(double) * n, hipMemcpyDeviceToHost, p->side);
     if (e == hipSuccess) e = hipStreamSynchronize(p->side);
     if (e != hipSuccess) return hip_fail(e, "collect");
     const lbm_status result = f->second;

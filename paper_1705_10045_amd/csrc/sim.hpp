@@ -25,7 +25,7 @@ struct lbm_sim {
     double* d_partials = nullptr;        // partial sums of lbm_reduce
     double* d_step_partials = nullptr;   // per-workgroup totals of lbm_step_reduce's last step
     long long step_partials_len = 0;     // doubles held by d_step_partials
-    double* d_scratch = nullptr;         // moment scratch (7n doubles), allocated on first use
+    double* d_scratch = nullptr;         // moment scratch and fields (10n doubles), allocated on first use
     double* d_eos_p = nullptr;           // tabulated EOS: reduced pressures and band per row
     double* d_eos_coex = nullptr;
     int red_blocks = 1;
