@@ -2,13 +2,19 @@
 // resident in one HBM arena and advanced together.
 //
 // Device side: a slot table (one SlotDesc per slot) and a flat work list of tiles: slot s owns
-// the global tile indices [tile_begin, tile_begin + ntiles).  One step of every active slot is
+// the global tile indices [tile_begin, tile_begin + ntiles).  One fused step of every active slot is
 // one launch of k_pool_step per kind of request present (periodic or with walls or gravity,
 // BGK or MRT) over a fixed grid that walks the work list, followed by k_pool_advance, which
 // flips each slot's buffer parity, counts its steps down and retires it when done or when its
 // error word is set.  steps_per_run such steps are captured into a HIP graph, one graph per set
-// of kinds, each captured once on first use; admissions and collections only rewrite the slot
+// of kinds and form of the step, each captured once on first use; admissions and collections only rewrite the slot
 // table between replays.
+//
+// While few nodes are resident, the fused tiles leave most of the chip idle and a step takes the
+// chain of one tile, 20 plane iterations of 5 to 9 us whatever the load.  Such replays run the
+// step as two launches instead (split_kernel.hpp): moments of all nodes into a bounded workspace,
+// then force and collision on small tiles (k_pool_moments, k_pool_collide).  Both forms give the same bits, so the choice is made
+// anew whenever the table is uploaded.
 //
 // Host side: first-fit allocation of slot buffers inside one arena allocated at creation
 // (admission by footprint never calls the allocator of the runtime), tickets, and the
@@ -31,6 +37,7 @@
 #include "../../include/lbm_mi355x.h"
 #include "kernels.hpp"
 #include "sim.hpp"
+#include "split_kernel.hpp"
 #include "step_kernel.hpp"
 
 namespace lbm {
@@ -47,25 +54,148 @@ struct SlotDesc {
     Phys phys;
     int tile_begin;
     int ntiles;
-    int parity;        // buf[parity] holds the current state
-    int active;        // 1 while steps remain and no error was flagged
     int kind;          // launch that serves the slot: kind_of(ext, mrt), ext 0 periodic, 1 walls
                        // or gravity (kExtWalls), 2 a tabulated EOS (kExtTable), mrt the MRT
                        // collision
     const double* eos_p;     // tabulated EOS: the request's copy of the table in the arena
     const double* eos_coex;
+    StepGeom split;          // tiles and z chunks of the two-launch step
+    void* scratch;           // its moments, in the pool's workspace (set with the work list)
+};
+
+// What a step changes of a slot, apart from its populations.
+struct SlotState {
+    int parity;        // buf[parity] holds the current state
+    int active;        // 1 while steps remain and no error was flagged
     long long remaining;
     long long steps_done;
 };
+
+// Host mirror of a slot.
+struct SlotEntry : SlotDesc, SlotState {};
 
 struct PoolHeader {
     int nslots;        // slots [0, nslots) are searched by the step kernel
     int total_tiles;
     int kind_tiles[6]; // tiles of the requests of each kind (SlotDesc::kind)
+    int total_blocks;  // two-launch step: blocks of kSplitThreads nodes, and tiles
+    int total_split;
 };
 
 constexpr int kPoolKinds = 6;
 __host__ __device__ constexpr int kind_of(int ext, bool mrt) { return ext + (mrt ? 3 : 0); }
+
+// First work item of this workgroup of a fixed grid over `total` items (-1: none).  XCD-aware order:
+// each XCD walks contiguous runs of the work list, so neighbouring tiles of one request share that
+// XCD's L2; a list shorter than the grid is spread over all of them.
+__device__ __forceinline__ int first_item(int total)
+{
+    const int n = min(total, (int)gridDim.x);
+    return (int)blockIdx.x < n ? xcd_logical_block(blockIdx.x, n) : -1;
+}
+
+// Slot that owns item t: the last one whose first item is at most t.
+__device__ __forceinline__ int slot_of(const int* __restrict__ begins, int nslots, int t)
+{
+    int lo = 0, hi = nslots - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (begins[mid] <= t) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
+__device__ __forceinline__ StepAux slot_aux(const SlotDesc& d, const double* table, double s0, double inv_ds,
+                                            int* err)
+{
+    StepAux aux;
+    aux.maxwell = table;
+    aux.tab_s0 = s0;
+    aux.tab_inv_ds = inv_ds;
+    aux.err = err;
+    aux.eos_p = d.eos_p;
+    aux.eos_coex = d.eos_coex;
+    aux.partials = nullptr;
+    return aux;
+}
+
+// State of a slot after a step that left the error word err.
+__device__ __forceinline__ SlotState advanced(SlotState st, int err)
+{
+    if (!st.active) return st;
+    st.parity ^= 1;
+    st.steps_done += 1;
+    st.remaining -= 1;
+    if (st.remaining <= 0 || err != 0) st.active = 0;
+    return st;
+}
+
+// The two-launch step over all slots.  Only the moments set error words, so the second launch
+// knows the state after the step: it writes that into `next`, which the next step reads as `state`
+// (a launch of k_pool_advance took 4.5 us of the 31 us of a step of one 64^3 request); with a null
+// `next` an advance launch follows.  begins[s] is the first node block of slot s and
+// begins[nmax + s] its first tile (nmax: length of the tables).
+template <int EXTK>
+__global__ void __launch_bounds__(kSplitThreads)
+k_pool_moments(const SlotDesc* __restrict__ slots, const SlotState* __restrict__ state,
+               const PoolHeader* __restrict__ hdr, const int* __restrict__ begins,
+               const double* __restrict__ table, double s0, double inv_ds, int* __restrict__ errs)
+{
+    const int total = hdr->total_blocks, nslots = hdr->nslots;
+    const int first = first_item(total);
+    if (first < 0) return;
+    for (int t = first; t < total; t += gridDim.x) {
+        const int s = slot_of(begins, nslots, t);
+        const SlotDesc& d = slots[s];
+        const SlotState st = state[s];
+        if (!st.active || d.kind % 3 != (EXTK == kExtNone ? 0 : (EXTK == kExtWalls ? 1 : 2))) continue;
+        const StepGeom g = d.split;
+        const Phys ph = d.phys;
+        const StepAux aux = slot_aux(d, table, s0, inv_ds, errs + s);
+        split_moments_node<19, float, float, EXTK>(d.buf[st.parity], d.scratch, g, ph, aux,
+                                                   (unsigned)(t - begins[s]) * kSplitThreads + threadIdx.x);
+    }
+}
+
+template <int EXTK, bool MRT>
+__global__ void __launch_bounds__(kSplitThreads, 3)
+k_pool_collide(const SlotDesc* __restrict__ slots, const SlotState* __restrict__ state,
+               SlotState* __restrict__ next, const PoolHeader* __restrict__ hdr, const int* __restrict__ begins,
+               const double* __restrict__ table, double s0, double inv_ds, int* __restrict__ errs)
+{
+    constexpr int kKind = kind_of(EXTK == kExtNone ? 0 : (EXTK == kExtWalls ? 1 : 2), MRT);
+    const int total = hdr->total_split, nslots = hdr->nslots;
+    const int first = first_item(total);
+    if (first < 0) return;
+    __shared__ SplitLds<float, kSplitTX, kSplitTY> lds;
+    for (int t = first; t < total; t += gridDim.x) {
+        const int s = slot_of(begins, nslots, t);
+        const SlotDesc& d = slots[s];
+        if (d.kind != kKind) continue;
+        const SlotState st = state[s];
+        const int local = t - begins[s];
+        if (next && local == 0 && threadIdx.x == 0) next[s] = advanced(st, errs[s]);
+        if (!st.active) continue;
+        const StepGeom g = d.split;
+        const Phys ph = d.phys;
+        const float* src = d.buf[st.parity];
+        float* dst = d.buf[1 - st.parity];
+        const void* scratch = d.scratch;
+        const StepAux aux = slot_aux(d, table, s0, inv_ds, errs + s);
+        // opaque to the compiler, which would else keep everything that depends on the thread
+        // alone in registers over all tiles (19 of them spilled, now 5)
+        unsigned tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        tid &= kSplitThreads - 1;
+        if constexpr (MRT)
+            split_collide_tile<19, float, float, kMrt, EXTK, false>(lds, src, dst, scratch, g, ph, aux, local, tid);
+        else if (ph.omega == 1.0)
+            split_collide_tile<19, float, float, kTauOne, EXTK, false>(lds, src, dst, scratch, g, ph, aux, local, tid);
+        else
+            split_collide_tile<19, float, float, kTauAny, EXTK, false>(lds, src, dst, scratch, g, ph, aux, local, tid);
+        __syncthreads();   // the next tile reuses the LDS
+    }
+}
 
 // One launch per kind of request (EXTK: kExtNone for periodic boxes, kExtWalls with walls or
 // gravity, kExtTable with a tabulated EOS; MRT: the MRT collision instead of BGK), each skipping
@@ -73,17 +203,18 @@ __host__ __device__ constexpr int kind_of(int ext, bool mrt) { return ext + (mrt
 // instantiation.
 template <int EXTK, bool MRT>
 __global__ void __launch_bounds__(kPoolThreads)
-k_pool_step(const SlotDesc* __restrict__ slots, const PoolHeader* __restrict__ hdr,
-            const double* __restrict__ table, double s0, double inv_ds, int* __restrict__ errs)
+k_pool_step(const SlotDesc* __restrict__ slots, const SlotState* __restrict__ state,
+            const PoolHeader* __restrict__ hdr, const double* __restrict__ table, double s0, double inv_ds,
+            int* __restrict__ errs)
 {
     constexpr int kKind = kind_of(EXTK == kExtNone ? 0 : (EXTK == kExtWalls ? 1 : 2), MRT);
     if (hdr->kind_tiles[kKind] == 0) return;
     __shared__ TileLds<19, float, float, kPoolTX, kPoolTY, true> lds;
     const int total = hdr->total_tiles;
     const int nslots = hdr->nslots;
-    // XCD-aware order: each XCD walks contiguous runs of the work list, so neighbouring tiles
-    // of one request share that XCD's L2
-    for (int t = xcd_logical_block(blockIdx.x, gridDim.x); t < total; t += gridDim.x) {
+    const int first = first_item(total);
+    if (first < 0) return;
+    for (int t = first; t < total; t += gridDim.x) {
         // slot owning tile t: last slot with tile_begin <= t (binary search, workgroup-uniform)
         int lo = 0, hi = nslots - 1;
         while (lo < hi) {
@@ -91,22 +222,15 @@ k_pool_step(const SlotDesc* __restrict__ slots, const PoolHeader* __restrict__ h
             if (slots[mid].tile_begin <= t) lo = mid; else hi = mid - 1;
         }
         const SlotDesc& d = slots[lo];
-        if (!d.active || t - d.tile_begin >= d.ntiles || d.kind != kKind) continue;
+        if (!state[lo].active || t - d.tile_begin >= d.ntiles || d.kind != kKind) continue;
         // workgroup-uniform copies, so the stores of the step cannot alias them
         const StepGeom g = d.geom;
         const Phys ph = d.phys;
-        const int parity = d.parity;
+        const int parity = state[lo].parity;
         const int local = t - d.tile_begin;
         const float* src = d.buf[parity];
         float* dst = d.buf[1 - parity];
-        StepAux aux;
-        aux.maxwell = table;
-        aux.tab_s0 = s0;
-        aux.tab_inv_ds = inv_ds;
-        aux.err = errs + lo;
-        aux.eos_p = d.eos_p;
-        aux.eos_coex = d.eos_coex;
-        aux.partials = nullptr;
+        const StepAux aux = slot_aux(d, table, s0, inv_ds, errs + lo);
         // each request's own collision: MRT, or BGK with tau = 1 (with the density prefetch)
         // or general; all share the workgroup's LDS
         if constexpr (MRT)
@@ -121,17 +245,12 @@ k_pool_step(const SlotDesc* __restrict__ slots, const PoolHeader* __restrict__ h
     }
 }
 
-__global__ void k_pool_advance(SlotDesc* __restrict__ slots, const PoolHeader* __restrict__ hdr,
+__global__ void k_pool_advance(SlotState* __restrict__ state, const PoolHeader* __restrict__ hdr,
                                const int* __restrict__ errs)
 {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= hdr->nslots) return;
-    SlotDesc& d = slots[s];
-    if (!d.active) return;
-    d.parity ^= 1;
-    d.steps_done += 1;
-    d.remaining -= 1;
-    if (d.remaining <= 0 || errs[s] != 0) d.active = 0;
+    state[s] = advanced(state[s], errs[s]);
 }
 
 }  // namespace lbm
@@ -151,9 +270,10 @@ struct lbm_pool {
     hipStream_t stream = nullptr;            // replays
     bool own_stream = false;
     hipStream_t side = nullptr;              // admissions and collections
-    SlotDesc* h_up = nullptr;                // pinned: the table as uploaded before a replay
+    SlotDesc* h_up = nullptr;                // pinned: the table as uploaded before a replay, and behind it
     PoolHeader* h_hdr = nullptr;             // pinned: its header
-    SlotDesc* h_rb = nullptr;                // pinned: the table read back after a replay
+    SlotState* h_state = nullptr;            // the slots' state and the work list (h_begins)
+    SlotState* h_rb = nullptr;               // pinned: the state read back after a replay
     int* h_errs = nullptr;                   // pinned: the error words read back after a replay
     hipEvent_t done = nullptr;               // end of the replay in flight and of its readback
     bool in_flight = false;
@@ -163,8 +283,10 @@ struct lbm_pool {
     std::map<size_t, size_t> free_blocks;   // offset -> size, coalesced
     int max_slots = 0, steps_per_run = 1;
     std::vector<PoolSlot> slots;
-    std::vector<SlotDesc> table;             // host mirror of the device slot table
+    std::vector<SlotEntry> table;            // host mirror of the device slot table
     SlotDesc* d_slots = nullptr;
+    SlotState* d_state = nullptr;            // behind d_slots: max_slots, and as many again that two-launch
+                                             // steps alternate with
     PoolHeader* d_hdr = nullptr;
     int* d_errs = nullptr;
     double* d_table = nullptr;
@@ -173,11 +295,16 @@ struct lbm_pool {
     double* d_scratch = nullptr;             // moment scratch (10 n doubles)
     double* d_red = nullptr;                 // reduction partials (kPoolRedBlocks x 5)
     double* d_totals = nullptr;              // per slot: totals at admission, then at the end
+    int* d_begins = nullptr;                 // two-launch step: first node block and tile per slot (behind d_state)
+    int* h_begins = nullptr;
+    char* workspace = nullptr;               // its moments (null: fused steps only)
+    size_t workspace_bytes = 0;
     // one graph per set of request kinds present (bit k: a slot of SlotDesc::kind k is
-    // active), captured on first use, so a replay launches only the kinds it serves
-    hipGraph_t graph[1 << kPoolKinds] = {};
-    hipGraphExec_t exec[1 << kPoolKinds] = {};
-    int kinds = 0;                           // kind set of the uploaded table
+    // active) and form of the step (bit kPoolKinds: two launches), captured on first use, so a
+    // replay launches only the kinds it serves
+    hipGraph_t graph[2 << kPoolKinds] = {};
+    hipGraphExec_t exec[2 << kPoolKinds] = {};
+    int kinds = 0;                           // kind set and form of the uploaded table
     bool dirty = true;
     long long next_ticket = 1;
     std::map<long long, int> ticket_slot;
@@ -249,12 +376,61 @@ StepGeom pool_geometry(const lbm_params& p)
     return g;
 }
 
+// Work list of the two-launch step for the active slots, and whether this replay takes it: where
+// its estimated time is below the fused form's and its moments fit the workspace.
+// Fused, per kind: 20 plane iterations (chunks of 16 and 4 more) per round of kPoolGrid tiles, 9.4 us
+// each in a full round and 5 us on an idle chip (MRT a tenth more), and 5 us for k_pool_advance.
+// Two launches: 4 us and a cost per lane of the tiles.  Measured, us per step, fused and two launches:
+// 32^3 114 and 12.4, 4 x 32^3 124 and 17.5, 64^3 138 and 28, 96^3 164 and 97, 2 x 96^3 182 and 183,
+// 3 x 96^3 328 and 254, 4 x 96^3 349 and 326, 2 x 128^3 367 and 411.
+bool plan_split(lbm_pool* p, const int* kind_tiles)
+{
+    if (!p->workspace) return false;
+    static const double lane_ps[2] = {94.0, 113.0};
+    double split_us = 4.0, fused_us = 5.0;
+    long long tiles = 0;
+    size_t need = 0;
+    for (int s = 0; s < p->max_slots; ++s) {
+        const SlotEntry& d = p->table[s];
+        if (!p->slots[s].used || !d.active) continue;
+        const long long t = (long long)d.split.ntx * d.split.nty * d.split.nz;
+        tiles += t;
+        split_us += 1e-6 * lane_ps[d.kind >= 3] * (double)(t * kSplitTX * kSplitTY);
+        need += (split_scratch_bytes(4, (long long)d.geom.pitch * d.geom.ny * d.geom.nz) + kAlign - 1) / kAlign * kAlign;
+    }
+    for (int k = 0; k < kPoolKinds; ++k) {
+        const int full = kind_tiles[k] / kPoolGrid, rest = kind_tiles[k] % kPoolGrid;
+        fused_us += (k >= 3 ? 1.1 : 1.0) * (kPoolChunk + 4) * (9.4 * full + (rest ? 5.0 + 4.4 * rest / kPoolGrid : 0.0));
+    }
+    if (need > p->workspace_bytes || !(split_us < fused_us)) return false;
+    const long long round = 3LL * kPoolGrid;
+    const int chunk = tiles <= round ? 1 : (tiles <= 16 * round ? 2 : 4);
+    int blocks = 0, split_tiles = 0;
+    size_t off = 0;
+    for (int s = 0; s < p->max_slots; ++s) {
+        SlotEntry& d = p->table[s];
+        p->h_begins[s] = blocks;
+        p->h_begins[p->max_slots + s] = split_tiles;
+        if (!p->slots[s].used || !d.active) continue;
+        StepGeom& g = d.split;
+        g.chunk = chunk < g.nz ? chunk : g.nz;
+        g.nchunks = (g.nz + g.chunk - 1) / g.chunk;
+        d.scratch = p->workspace + off;
+        off += (split_scratch_bytes(4, (long long)g.pitch * g.ny * g.nz) + kAlign - 1) / kAlign * kAlign;
+        blocks += (int)(((long long)g.nx * g.ny * g.nz + kSplitThreads - 1) / kSplitThreads);
+        split_tiles += g.ntx * g.nty * g.nchunks;
+    }
+    p->h_hdr->total_blocks = blocks;
+    p->h_hdr->total_split = split_tiles;
+    return true;
+}
+
 // Rebuild the work list (tile prefix over slots in index order) and upload the table.
 lbm_status upload_table(lbm_pool* p)
 {
     int total = 0, nslots = 0, kind_tiles[kPoolKinds] = {}, kinds = 0;
     for (int s = 0; s < p->max_slots; ++s) {
-        SlotDesc& d = p->table[s];
+        SlotEntry& d = p->table[s];
         d.tile_begin = total;
         if (p->slots[s].used && d.active) {
             d.ntiles = d.geom.ntx * d.geom.nty * d.geom.nchunks;
@@ -272,10 +448,18 @@ lbm_status upload_table(lbm_pool* p)
     p->h_hdr->nslots = nslots;
     p->h_hdr->total_tiles = total;
     for (int k = 0; k < kPoolKinds; ++k) p->h_hdr->kind_tiles[k] = kind_tiles[k];
-    memcpy(p->h_up, p->table.data(), sizeof(SlotDesc) * p->max_slots);
+    if (plan_split(p, kind_tiles)) kinds |= 1 << kPoolKinds;
+    for (int s = 0; s < p->max_slots; ++s) {
+        p->h_up[s] = p->table[s];
+        p->h_state[s] = p->table[s];
+    }
     hipError_t e = hipMemcpyAsync(p->d_slots, p->h_up, sizeof(SlotDesc) * p->max_slots,
                                   hipMemcpyHostToDevice, p->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(p->d_state, p->h_state, sizeof(SlotState) * p->max_slots, hipMemcpyHostToDevice, p->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(p->d_hdr, p->h_hdr, sizeof(PoolHeader), hipMemcpyHostToDevice, p->stream);
+    if (e == hipSuccess && (kinds >> kPoolKinds))
+        e = hipMemcpyAsync(p->d_begins, p->h_begins, sizeof(int) * 2 * p->max_slots, hipMemcpyHostToDevice, p->stream);
     if (e != hipSuccess) return hip_fail(e, "pool table upload");
     p->kinds = kinds;
     p->dirty = false;
@@ -290,10 +474,42 @@ lbm_status capture_graph(lbm_pool* p, int kinds)
     if (e != hipSuccess) return hip_fail(e, "graph capture begin");
     const int adv_blocks = (p->max_slots + 255) / 256;
     for (int i = 0; i < p->steps_per_run; ++i) {
+        if (kinds >> kPoolKinds) {
+            // steps go from one half of d_state to the other and back; an odd last step advances its half in place
+            const bool in_place = i % 2 == 0 && i + 1 == p->steps_per_run;
+            const SlotState* state = p->d_state + (i % 2) * p->max_slots;
+            SlotState* next = in_place ? nullptr : p->d_state + (1 - i % 2) * p->max_slots;
+            const int mgrid = 8 * kPoolGrid, cgrid = 3 * kPoolGrid;   // workgroups resident at once
+#define LBM_POOL_MOMENTS(EXTK)                                                                            \
+    if (kinds & ((1 << kind_of(EXTK, false)) | (1 << kind_of(EXTK, true))))                               \
+    hipLaunchKernelGGL((k_pool_moments<EXTK == 0 ? kExtNone : (EXTK == 1 ? kExtWalls : kExtTable)>),      \
+                       dim3(mgrid), dim3(kSplitThreads), 0, p->stream, p->d_slots, state, p->d_hdr,       \
+                       p->d_begins, p->d_table, p->tab_s0, p->tab_inv_ds, p->d_errs)
+#define LBM_POOL_COLLIDE(EXTK, MRT)                                                                       \
+    if (kinds & (1 << kind_of(EXTK, MRT)))                                                                \
+    hipLaunchKernelGGL((k_pool_collide<EXTK == 0 ? kExtNone : (EXTK == 1 ? kExtWalls : kExtTable), MRT>), \
+                       dim3(cgrid), dim3(kSplitThreads), 0, p->stream, p->d_slots, state, next, p->d_hdr, \
+                       p->d_begins + p->max_slots, p->d_table, p->tab_s0, p->tab_inv_ds, p->d_errs)
+            LBM_POOL_MOMENTS(0);
+            LBM_POOL_MOMENTS(1);
+            LBM_POOL_MOMENTS(2);
+            LBM_POOL_COLLIDE(0, false);
+            LBM_POOL_COLLIDE(1, false);
+            LBM_POOL_COLLIDE(2, false);
+            LBM_POOL_COLLIDE(0, true);
+            LBM_POOL_COLLIDE(1, true);
+            LBM_POOL_COLLIDE(2, true);
+#undef LBM_POOL_MOMENTS
+#undef LBM_POOL_COLLIDE
+            if (in_place)
+                hipLaunchKernelGGL(k_pool_advance, dim3(adv_blocks), dim3(256), 0, p->stream, p->d_state,
+                                   p->d_hdr, p->d_errs);
+            continue;
+        }
 #define LBM_POOL_LAUNCH(EXTK, MRT)                                                                       \
     if (kinds & (1 << kind_of(EXTK == kExtNone ? 0 : (EXTK == kExtWalls ? 1 : 2), MRT)))                  \
         hipLaunchKernelGGL((k_pool_step<EXTK, MRT>), dim3(kPoolGrid), dim3(kPoolThreads), 0, p->stream,      \
-                           p->d_slots, p->d_hdr, p->d_table, p->tab_s0, p->tab_inv_ds, p->d_errs);
+                           p->d_slots, p->d_state, p->d_hdr, p->d_table, p->tab_s0, p->tab_inv_ds, p->d_errs);
         LBM_POOL_LAUNCH(kExtNone, false)
         LBM_POOL_LAUNCH(kExtWalls, false)
         LBM_POOL_LAUNCH(kExtTable, false)
@@ -301,7 +517,7 @@ lbm_status capture_graph(lbm_pool* p, int kinds)
         LBM_POOL_LAUNCH(kExtWalls, true)
         LBM_POOL_LAUNCH(kExtTable, true)
 #undef LBM_POOL_LAUNCH
-        hipLaunchKernelGGL(k_pool_advance, dim3(adv_blocks), dim3(256), 0, p->stream, p->d_slots,
+        hipLaunchKernelGGL(k_pool_advance, dim3(adv_blocks), dim3(256), 0, p->stream, p->d_state,
                            p->d_hdr, p->d_errs);
     }
     e = hipStreamEndCapture(p->stream, &p->graph[kinds]);
@@ -323,8 +539,8 @@ lbm_status finish_replay(lbm_pool* p)
     for (int s = 0; s < p->max_slots; ++s) {
         PoolSlot& ps = p->slots[s];
         if (!ps.used || ps.ticket != p->launched[s]) continue;
-        SlotDesc& d = p->table[s];
-        const SlotDesc& r = p->h_rb[s];
+        SlotEntry& d = p->table[s];
+        const SlotState& r = p->h_rb[s];
         d.parity = r.parity;
         d.active = r.active;
         d.remaining = r.remaining;
@@ -359,7 +575,7 @@ lbm_status launch_replay(lbm_pool* p)
     for (int s = 0; s < p->max_slots; ++s) p->launched[s] = p->slots[s].used ? p->slots[s].ticket : -1;
     hipError_t e = hipGraphLaunch(p->exec[p->kinds], p->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(p->h_rb, p->d_slots, sizeof(SlotDesc) * p->max_slots, hipMemcpyDeviceToHost, p->stream);
+        e = hipMemcpyAsync(p->h_rb, p->d_state, sizeof(SlotState) * p->max_slots, hipMemcpyDeviceToHost, p->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(p->h_errs, p->d_errs, sizeof(int) * p->max_slots, hipMemcpyDeviceToHost, p->stream);
     if (e == hipSuccess) e = hipEventRecord(p->done, p->stream);
@@ -401,18 +617,20 @@ lbm_status lbm_pool_create(size_t hbm_budget_bytes, int max_slots, int steps_per
     p->max_slots = max_slots;
     p->steps_per_run = steps_per_run;
     p->slots.assign(max_slots, PoolSlot());
-    p->table.assign(max_slots, SlotDesc());
-    memset(p->table.data(), 0, sizeof(SlotDesc) * max_slots);
+    p->table.assign(max_slots, SlotEntry());
+    memset(static_cast<void*>(p->table.data()), 0, sizeof(SlotEntry) * max_slots);
     p->launched.assign(max_slots, -1);
     const long long nmax = (long long)kPoolMaxEdge * kPoolMaxEdge * kPoolMaxEdge;
     hipError_t e = hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&p->done, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&p->h_up, sizeof(SlotDesc) * max_slots, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&p->h_rb, sizeof(SlotDesc) * max_slots, hipHostMallocDefault);
+    // descriptors, state (two halves on the device) and work list of the slots in one allocation each
+    const size_t table_bytes = (sizeof(SlotDesc) + 2 * sizeof(SlotState) + 2 * sizeof(int)) * max_slots;
+    if (e == hipSuccess) e = hipHostMalloc((void**)&p->h_up, table_bytes, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&p->h_rb, sizeof(SlotState) * max_slots, hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc((void**)&p->h_hdr, sizeof(PoolHeader), hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc((void**)&p->h_errs, sizeof(int) * max_slots, hipHostMallocDefault);
     if (e == hipSuccess) e = hipMalloc((void**)&p->arena, p->budget);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_slots, sizeof(SlotDesc) * max_slots);
+    if (e == hipSuccess) e = hipMalloc((void**)&p->d_slots, table_bytes);
     if (e == hipSuccess) e = hipMalloc((void**)&p->d_hdr, sizeof(PoolHeader));
     if (e == hipSuccess) e = hipMalloc((void**)&p->d_errs, sizeof(int) * max_slots);
     if (e == hipSuccess) e = hipMalloc((void**)&p->d_staging, sizeof(double) * 5 * nmax);
@@ -421,7 +639,18 @@ lbm_status lbm_pool_create(size_t hbm_budget_bytes, int max_slots, int steps_per
     if (e == hipSuccess) e = hipMalloc((void**)&p->d_totals, sizeof(double) * 10 * max_slots);
     if (e == hipSuccess) e = hipMalloc((void**)&p->d_table, sizeof(double) * 2 * kMaxwellPoints);
     if (e != hipSuccess) { lbm_status r = hip_fail(e, "pool allocation"); lbm_pool_destroy(p); return r; }
+    p->h_state = reinterpret_cast<SlotState*>(p->h_up + max_slots);
+    p->h_begins = reinterpret_cast<int*>(p->h_state + 2 * max_slots);
+    p->d_state = reinterpret_cast<SlotState*>(p->d_slots + max_slots);
+    p->d_begins = reinterpret_cast<int*>(p->d_state + 2 * max_slots);
     p->free_blocks[0] = p->budget;
+    // the two-launch step's workspace: an eighth of the arena holds the moments of all it can hold
+    // (36 of 304 bytes per node), and beyond 7 million nodes the fused form is as fast
+    p->workspace_bytes = std::min(p->budget / 8, (size_t)256 << 20);
+    if (hipMalloc((void**)&p->workspace, p->workspace_bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        p->workspace = nullptr;
+    }
     // table of the band limits, the same one every simulation uses
     std::vector<double> tab(2 * kMaxwellPoints);
     const double s_lo = std::sqrt(1.0 - kLatentTmax), s_hi = std::sqrt(1.0 - kLatentTmin);
@@ -436,9 +665,10 @@ lbm_status lbm_pool_create(size_t hbm_budget_bytes, int max_slots, int steps_per
     if (e == hipSuccess) e = hipMemsetAsync(p->d_errs, 0, sizeof(int) * max_slots, p->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
     if (e != hipSuccess) { lbm_status r = hip_fail(e, "pool setup"); lbm_pool_destroy(p); return r; }
-    // the graph of the common kind set (periodic BGK requests only) up front
+    // the graphs of the common kind set (periodic BGK requests only) up front
     lbm_status st = upload_table(p);
     if (st == LBM_OK) st = capture_graph(p, 1);
+    if (st == LBM_OK && p->workspace) st = capture_graph(p, 1 | (1 << kPoolKinds));
     if (st != LBM_OK) { lbm_pool_destroy(p); return st; }
     *out = p;
     return LBM_OK;
@@ -485,11 +715,15 @@ lbm_status lbm_pool_submit(lbm_pool* p, const lbm_params* params, const double* 
     ps.params.eos_coex = nullptr;
     ps.nsteps = nsteps;
     ps.ticket = p->next_ticket++;
-    SlotDesc& d = p->table[slot];
+    SlotEntry& d = p->table[slot];
     memset(&d, 0, sizeof(d));
     d.buf[0] = (float*)(p->arena + off);
     d.buf[1] = (float*)(p->arena + off + half_al);
     d.geom = pool_geometry(*params);
+    d.split = d.geom;
+    d.split.ntx = (params->nx + kSplitTX - 1) / kSplitTX;
+    d.split.nty = (params->ny + kSplitTY - 1) / kSplitTY;
+    set_reciprocals(d.split);
     d.phys = make_phys(*params);
     d.parity = 0;
     d.active = 1;
@@ -575,7 +809,7 @@ lbm_status lbm_pool_collect(lbm_pool* p, long long ticket, double* rho, double* 
     if (f == p->finished.end()) { set_error("ticket %lld has not finished", ticket); return LBM_EBUSY; }
     const int s = it->second;
     PoolSlot& ps = p->slots[s];
-    const SlotDesc& d = p->table[s];
+    const SlotEntry& d = p->table[s];
     if (lbm_status sd = use_device(p->device); sd != LBM_OK) return sd;
     const long long n = (long long)ps.params.nx * ps.params.ny * ps.params.nz;
     double* scr = p->d_scratch;
@@ -596,7 +830,7 @@ lbm_status lbm_pool_collect(lbm_pool* p, long long ticket, double* rho, double* 
     p->ticket_slot.erase(it);
     p->finished.erase(f);
     ps = PoolSlot();
-    memset(&p->table[s], 0, sizeof(SlotDesc));
+    memset(static_cast<void*>(&p->table[s]), 0, sizeof(SlotEntry));
     p->dirty = true;
     if (result != LBM_OK) set_error("request %lld left the EOS domain", ticket);
     return result;
@@ -613,7 +847,7 @@ lbm_status lbm_pool_totals(lbm_pool* p, long long ticket, double initial[5], dou
         return LBM_EBUSY;
     }
     const int s = it->second;
-    const SlotDesc& d = p->table[s];
+    const SlotEntry& d = p->table[s];
     if (lbm_status sd = use_device(p->device); sd != LBM_OK) return sd;
     double h[10];
     double* d_tot = p->d_totals + 10 * s;
@@ -649,11 +883,12 @@ lbm_status lbm_pool_destroy(lbm_pool* p)
     (void)hipSetDevice(p->device);
     if (p->stream) (void)hipStreamSynchronize(p->stream);
     if (p->side) (void)hipStreamSynchronize(p->side);
-    for (int k = 0; k < (1 << kPoolKinds); ++k) {
+    for (int k = 0; k < (2 << kPoolKinds); ++k) {
         if (p->exec[k]) (void)hipGraphExecDestroy(p->exec[k]);
         if (p->graph[k]) (void)hipGraphDestroy(p->graph[k]);
     }
     if (p->arena) (void)hipFree(p->arena);
+    if (p->workspace) (void)hipFree(p->workspace);
     if (p->d_slots) (void)hipFree(p->d_slots);
     if (p->d_hdr) (void)hipFree(p->d_hdr);
     if (p->d_errs) (void)hipFree(p->d_errs);

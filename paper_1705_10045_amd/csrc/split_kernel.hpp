@@ -67,14 +67,14 @@ struct SplitFields {
 // Wavefronts of 256-thread workgroups, one node per thread.
 constexpr int kSplitThreads = 256;
 
+// Moments of node `id` (x fastest) of the box described by g.
 template <int Q, class S, class R, int EXT>
-__global__ void __launch_bounds__(kSplitThreads)
-k_split_moments(const S* __restrict__ src, void* __restrict__ scratch, const StepGeom g,
-                const Phys ph, const StepAux aux)
+__device__ __forceinline__ void split_moments_node(const S* __restrict__ src, void* __restrict__ scratch,
+                                                   const StepGeom& g, const Phys& ph, const StepAux& aux,
+                                                   const unsigned id)
 {
     using L = Lattice<Q>;
     const unsigned n = (unsigned)g.nx * (unsigned)g.ny * (unsigned)g.nz;
-    const unsigned id = (unsigned)xcd_logical_block(blockIdx.x, gridDim.x) * kSplitThreads + threadIdx.x;
     if (id >= n) return;
     const PopIO<S, kAddrBuf> io(src, nullptr, g.plane, 2 * Q);
     const unsigned nxy = (unsigned)g.pitch * (unsigned)g.ny;
@@ -124,6 +124,15 @@ k_split_moments(const S* __restrict__ src, void* __restrict__ scratch, const Ste
     f.store(f.j(2), own, R(djz));
 }
 
+template <int Q, class S, class R, int EXT>
+__global__ void __launch_bounds__(kSplitThreads)
+k_split_moments(const S* __restrict__ src, void* __restrict__ scratch, const StepGeom g,
+                const Phys ph, const StepAux aux)
+{
+    split_moments_node<Q, S, R, EXT>(src, scratch, g, ph, aux,
+                                     (unsigned)xcd_logical_block(blockIdx.x, gridDim.x) * kSplitThreads + threadIdx.x);
+}
+
 // LDS of one workgroup of k_split_collide: a ring of Phi planes on the tile + 2-halo (the force of
 // plane zf reads zf - 1 .. zf + 1 while zf + 2 is written; the first five planes of a chunk are
 // loaded at once), and rho, T, u*x, u*y on the tile + 1-halo for the planes zf and zf - 1 (written
@@ -149,10 +158,14 @@ constexpr int kSplitTX = 32, kSplitTY = 8;
 // Maxwell table's cell and the scratch of the next planes are requested first, the pulls last,
 // all before the force.  Lanes of a ragged tile beyond the box keep the control flow uniform:
 // their pulls and stores carry an offset beyond the buffer, which the hardware drops.
+// All threads of the workgroup call it, for tile `lb` (x fastest, then y, then z chunk); a caller
+// that runs several tiles puts a barrier between them.
 template <int Q, class S, class R, int NMODE, int EXT, bool RED>
-__global__ void __launch_bounds__(kSplitThreads, sizeof(R) == 4 ? 3 : 2)
-k_split_collide(const S* __restrict__ src, S* __restrict__ dst, const void* __restrict__ scratch,
-                const StepGeom g, const Phys ph, const StepAux aux)
+__device__ __forceinline__ void split_collide_tile(SplitLds<R, kSplitTX, kSplitTY>& lds,
+                                                   const S* __restrict__ src, S* __restrict__ dst,
+                                                   const void* __restrict__ scratch, const StepGeom& g,
+                                                   const Phys& ph, const StepAux& aux, const int lb,
+                                                   const int tid, double (*red)[5] = nullptr)
 {
     using L = Lattice<Q>;
     constexpr int TX = kSplitTX, TY = kSplitTY, NTH = kSplitThreads;
@@ -163,13 +176,10 @@ k_split_collide(const S* __restrict__ src, S* __restrict__ dst, const void* __re
     constexpr bool WN = NMODE != kTauOne;
     static_assert(NE <= 2 * NTH && NH <= NTH, "slots per thread");
     constexpr unsigned kDropped = 0xfffffffcu;   // beyond every buffer (states are under 4 GB)
-    __shared__ Lds lds;
 
-    const int lb = xcd_logical_block(blockIdx.x, gridDim.x, g.resident);
     const PopIO<S, kAddrBuf> io(src, dst, g.plane, 2 * Q);
     const unsigned nxy = (unsigned)g.pitch * (unsigned)g.ny;
     const SplitFields<R> m(const_cast<void*>(scratch), nxy * (unsigned)g.nz);
-    const int tid = threadIdx.x;
     const int trow = div_uniform(lb, g.inv_ntx), tiz = div_uniform(trow, g.inv_nty);
     const int tix = lb - trow * g.ntx, tiy = trow - tiz * g.nty;
     const int x0 = tix * TX, y0 = tiy * TY, z0 = tiz * g.chunk;
@@ -474,7 +484,6 @@ k_split_collide(const S* __restrict__ src, S* __restrict__ dst, const void* __re
 
     if constexpr (RED) {
         // the wavefronts' sums by shuffles, then the wavefronts in order
-        __shared__ double red[NTH / 64][5];
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
             double v = nsum[q];
@@ -489,6 +498,21 @@ k_split_collide(const S* __restrict__ src, S* __restrict__ dst, const void* __re
             for (int w = 0; w < NTH / 64; ++w) t += red[w][tid];
             aux.partials[(long long)lb * 5 + tid] = t;
         }
+    }
+}
+
+template <int Q, class S, class R, int NMODE, int EXT, bool RED>
+__global__ void __launch_bounds__(kSplitThreads, sizeof(R) == 4 ? 3 : 2)
+k_split_collide(const S* __restrict__ src, S* __restrict__ dst, const void* __restrict__ scratch,
+                const StepGeom g, const Phys ph, const StepAux aux)
+{
+    __shared__ SplitLds<R, kSplitTX, kSplitTY> lds;
+    const int lb = xcd_logical_block(blockIdx.x, gridDim.x, g.resident);
+    if constexpr (RED) {
+        __shared__ double red[kSplitThreads / 64][5];
+        split_collide_tile<Q, S, R, NMODE, EXT, true>(lds, src, dst, scratch, g, ph, aux, lb, threadIdx.x, red);
+    } else {
+        split_collide_tile<Q, S, R, NMODE, EXT, false>(lds, src, dst, scratch, g, ph, aux, lb, threadIdx.x);
     }
 }
 
