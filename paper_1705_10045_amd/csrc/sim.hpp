@@ -17,6 +17,7 @@ struct lbm_sim {
     int cus = 256;                       // compute units of the device
     hipStream_t stream = nullptr;
     bool own_stream = false;
+    char* memory = nullptr;             // holds buf, d_err, d_table, d_partials and often d_split
     void* buf[2] = {nullptr, nullptr};  // population buffers; buf[cur] holds the current state
     int cur = 0;
     long long step = 0;
@@ -35,6 +36,7 @@ struct lbm_sim {
     bool split = false;                  // the step runs as two launches (split_kernel.hpp)
     lbm::StepGeom split_geom;            // tiles and z chunks of their collision launch
     void* d_split = nullptr;             // their moment scratch
+    bool own_split = false;              // allocated after the start, by itself
     lbm::MultiGeom multi{};              // D2Q9: steps taken per launch (0: single steps) and their tiles
 };
 
