@@ -535,7 +535,8 @@ MultiGeom multi_geometry(const lbm_params& p, int tx, int ty, int steps)
 // than single steps (300^2 FP64: 10.3 us per step against 9.3).  Among those, the tile and the
 // step count of least time per step, a launch taking about 2 us and each of its steps 2.1 us
 // plus 0.21 us per further wavefront of the region (measured over 12 tiles and 1 to 16 steps).
-// FP64 times per step: 1000 nodes 6.2 -> 2.2 us, 128^2 7.2 -> 4.4 us, 256^2 7.9 -> 6.1 us.
+// FP64 times per step: 1000 nodes 6.2 -> 2.2 us, 128^2 7.2 -> 4.4 us, 256^2 7.9 -> 6.1 us; 300^2 8.6
+// against 9.1 for single steps, but 350^2 11.1 against 10.2 (FP32 7.9 against 8.6).
 MultiGeom plan_multi(const lbm_params& p, int cus)
 {
     MultiGeom best{};
@@ -559,6 +560,8 @@ MultiGeom plan_multi(const lbm_params& p, int cus)
             }
         }
     }
+    // regions of one step beyond 9 wavefronts: single steps are as fast for FP64 populations
+    if (best.steps == 1 && p.storage_bytes == 8 && best.rx * best.ry > 576) return MultiGeom{};
     return best;
 }
 

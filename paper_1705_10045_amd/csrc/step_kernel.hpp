@@ -752,4 +752,16 @@ k_step(const S* __restrict__ src, S* __restrict__ dst, const StepGeom g, const P
     }
 }
 
+// The step held to the registers of WAVES wavefronts per SIMD.
+template <int WAVES, int Q, class S, class R, int TX, int TY, int NTH, bool PIPE, int ADDR, int NMODE,
+          bool STASH, int EXT>
+__global__ void __launch_bounds__(NTH, WAVES)
+k_step_waves(const S* __restrict__ src, S* __restrict__ dst, const StepGeom g, const Phys ph,
+             const StepAux aux)
+{
+    __shared__ TileLds<Q, S, R, TX, TY, STASH> lds;
+    const int lb = xcd_logical_block(blockIdx.x, gridDim.x, g.resident);
+    step_tile<Q, S, R, TX, TY, NTH, PIPE, ADDR, NMODE, STASH, EXT>(lds, src, dst, g, ph, aux, lb);
+}
+
 }  // namespace lbm
