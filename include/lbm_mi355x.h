@@ -200,9 +200,12 @@ lbm_status lbm_reduce(lbm_sim* sim, double out[5]);
  * of the FP64 sums), so the state is not read a second time.  The fields are bitwise those of
  * lbm_step.  The fused form exists for the lbm_set_launch variants 0, 5 and 7 of FP32 D3Q19,
  * 0 of FP64 D3Q19, 0 and 2 of FP32 D2Q9 and 0 of FP64 D2Q9 (every variant lbm_init starts
- * with); the others run the step and then the separate reduction.  The first call, and any
- * call after lbm_set_launch raised the workgroup count, allocates a device array of 5 doubles
- * per workgroup that the simulation keeps until lbm_free.  Synchronises; returns
+ * with); the others run the step and then the separate reduction.  A simulation whose launch was
+ * not set takes its last D3Q19 step as two launches (states under 4 GB), which sum the totals
+ * faster.  The first call, and any call after lbm_set_launch raised the workgroup count,
+ * allocates a device array of 5 doubles per workgroup (and, for the two launches, a scratch of
+ * 36 or 56 bytes per node; without room for it the fused form runs) that the simulation keeps
+ * until lbm_free.  Synchronises; returns
  * LBM_EUNSTABLE like lbm_step (out is then not meaningful) and LBM_EINVAL for nsteps < 1 or
  * a NULL out. */
 lbm_status lbm_step_reduce(lbm_sim* sim, int nsteps, double out[5]);
@@ -228,7 +231,8 @@ lbm_status lbm_free(lbm_sim* sim);
 const char* lbm_last_error(void);
 
 /* Launch geometry of the fused step kernel: tile width/height in nodes, z-chunk length and
- * number of workgroups per step (for profiling reports). */
+ * number of workgroups per step (for profiling reports).  Small and ragged boxes run other
+ * kernels by default (see lbm_set_launch), which this does not describe. */
 lbm_status lbm_launch_info(const lbm_sim* sim, int info[4]);
 
 /* The launch lbm_init chooses for these parameters (default variant, automatic z chunk) on a
@@ -243,7 +247,10 @@ lbm_status lbm_launch_plan(const lbm_params* params, int cus, int info[4]);
  * D2Q9 three: 32x8, 32x16 and 64x8 tiles) and the z-chunk length (0 = automatic).  lbm_init
  * starts with variant 0, except for FP32 D3Q19 states of 4 GB and more whose x extent tiles
  * at 64 with no more idle columns than at 32: those start with variant 7 (64x8 tiles, global
- * addressing).  Results do not depend on the choice (the per-node arithmetic is the same);
+ * addressing).  Before the first call of lbm_set_launch the library may take another form of the
+ * step where it is faster: two launches per step for small and ragged D3Q19 boxes and most FP64
+ * ones, several steps per launch for small D2Q9 boxes; after it the fused kernel runs, one launch
+ * per step.  Results do not depend on any of these choices (the per-node arithmetic is the same);
  * only speed does.  LBM_EINVAL for an unknown variant or a negative chunk. */
 lbm_status lbm_set_launch(lbm_sim* sim, int variant, int chunk);
 
@@ -273,7 +280,9 @@ typedef struct lbm_pool lbm_pool;
 
 /* Create a pool on the current device.  params of submitted requests must use lattice 19,
  * storage 4 and edges up to max_edge; walls, gravity, a tabulated EOS and the MRT collision are
- * accepted (each kind of request runs in its own launch of the batched step). */
+ * accepted (each kind of request runs in its own launch of the batched step).  Beside the budget
+ * the pool holds its staging buffers and, if there is room, a workspace of an eighth of the budget
+ * (256 MiB at most) for the form of the step that it takes under a light load. */
 lbm_status lbm_pool_create(size_t hbm_budget_bytes, int max_slots, int steps_per_run,
                            void* stream, lbm_pool** out);
 
