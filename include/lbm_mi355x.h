@@ -153,7 +153,10 @@ lbm_status lbm_init(const lbm_params* params, const double* rho0, const double* 
 lbm_status lbm_step(lbm_sim* sim, int nsteps);
 
 /* Enqueue nsteps time steps without synchronising (for timing and overlap); errors found on
- * the device are reported by the next lbm_step, lbm_check or lbm_moments. */
+ * the device are reported by the next lbm_step, lbm_check or lbm_moments.  The calls may be
+ * captured into a graph of the caller's stream: one of an even number of steps leaves the state in
+ * the device buffer where it found it, so its replays advance the state (the step count is that of
+ * the calls, not of the replays). */
 lbm_status lbm_step_async(lbm_sim* sim, int nsteps);
 
 /* Synchronise the stream and report the device error word (LBM_OK or LBM_EUNSTABLE). */

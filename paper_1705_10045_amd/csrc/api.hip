@@ -629,11 +629,20 @@ lbm_status enqueue_steps(lbm_sim* s, int nsteps)
         set_error("simulation is not fully initialised (null device pointer)");
         return LBM_EDEVICE;
     }
-    for (int i = 0, taken = 1; i < nsteps; i += taken) {
+    const bool multi = s->multi.steps > 0 && !s->launch_set;
+    // launches of several steps: even in number for an even number of steps and odd for an odd one, so that
+    // the state's buffer follows the step count in every form (a caller's graph of an even number of
+    // steps leaves the state where it found it and can be replayed), and of like lengths
+    int launches = nsteps;
+    if (multi) {
+        launches = (nsteps + s->multi.steps - 1) / s->multi.steps;
+        launches += (launches ^ nsteps) & 1;
+    }
+    for (int i = 0, taken = 1; i < nsteps; i += taken, --launches) {
         hipError_t e;
         taken = 1;
-        if (s->multi.steps > 0 && !s->launch_set) {
-            taken = nsteps - i < s->multi.steps ? nsteps - i : s->multi.steps;
+        if (multi) {
+            taken = (nsteps - i + launches - 1) / launches;
             e = enqueue_multi(s, taken);
         } else if (s->split) {
             e = launch_split_moments(s->p.storage_bytes, s->buf[s->cur], s->d_split, s->split_geom, s->phys,
