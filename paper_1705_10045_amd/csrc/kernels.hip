@@ -80,8 +80,9 @@ __global__ void k_init(S* __restrict__ buf, const double* __restrict__ rho0,
 
 // Moments of the current state in FP64, one node per thread: rho, E and T where an output is
 // given; for u*, rho and Phi into the scratch and j into the u* output itself, which the second
-// kernel turns into u* in place.  Bound by its traffic (152 bytes read and 56 written per FP32
-// D3Q19 node; 5.2 TB/s at 128^3).
+// kernel turns into u* in place.  That kernel reads nothing else the caller gave: outputs it does not
+// want may share an array, or be that of u*.  Bound by its traffic (152 bytes read and 64 written per
+// FP32 D3Q19 node).
 struct MomentOut {
     double *rho, *us, *E, *T;       // any may be null
     double *rho_tmp, *phi;          // used with us
@@ -128,7 +129,7 @@ __global__ void k_moments_a(const S* __restrict__ buf, const MomentOut out, cons
     if (out.E) out.E[i] = E;
     if (out.T) out.T[i] = T;
     if (out.us) {
-        if (!out.rho) out.rho_tmp[i] = rho;
+        out.rho_tmp[i] = rho;
         out.phi[i] = sqrt(phi2);
         out.us[i] = jx;
         out.us[(long long)n + i] = jy;
@@ -164,7 +165,7 @@ __global__ void k_moments_b(const MomentOut out, const BoxIndex box, Phys ph)
             s2[a] += G * p * c[a];
         }
     }
-    const double rho = out.rho ? out.rho[i] : out.rho_tmp[i];
+    const double rho = out.rho_tmp[i];
     const double phi = Phi[i];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
