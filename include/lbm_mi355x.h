@@ -204,8 +204,8 @@ lbm_status lbm_reduce(lbm_sim* sim, double out[5]);
  * lbm_step.  The fused form exists for the lbm_set_launch variants 0, 5 and 7 of FP32 D3Q19,
  * 0 of FP64 D3Q19, 0 and 2 of FP32 D2Q9 and 0 of FP64 D2Q9 (every variant lbm_init starts
  * with); the others run the step and then the separate reduction.  A simulation whose launch was
- * not set takes its last D3Q19 step as two launches (states under 4 GB), which sum the totals
- * faster.  The first call, and any call after lbm_set_launch raised the workgroup count,
+ * not set takes its last D3Q19 step as two launches where they form the totals faster (states under
+ * 4 GB: tau = 1, MRT in FP64, and small boxes of the other collisions).  The first call, and any call after lbm_set_launch raised the workgroup count,
  * allocates a device array of 5 doubles per workgroup (and, for the two launches, a scratch of
  * 36 or 56 bytes per node; without room for it the fused form runs) that the simulation keeps
  * until lbm_free.  Synchronises; returns

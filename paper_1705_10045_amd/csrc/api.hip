@@ -500,6 +500,40 @@ bool split_default(const lbm_params& p, const StepGeom& fused, const StepGeom& s
     return two < 0.95 * (double)rounds * (fused.chunk + 4) * plane_us[wide][kind];
 }
 
+// Whether the step that forms the totals runs as two launches.  For tau = 1, and for MRT in FP64, it does
+// wherever it can: it was the faster form in all of 23 boxes from 48^3 to 200^3 (FP32 1 to 37%: the fused form's
+// totals cost its prefetch; FP64 10 to 61%: they cost it registers).  For the other collisions the totals leave
+// the two-launch form's collision short of registers, and where the fused launch fills its rounds it is up to
+// 16% faster (FP32 tau = 0.8 at 128^3 222 us against 250, 256x256x64 429 against 487).  Their estimates follow
+// the measured times of the 23 boxes within 10%:
+//   - two launches: 5 us and, per lane of the padded tiles, 111 / 115 ps for FP32 with BGK / MRT and 168 ps for
+//     FP64 while two states fit the 256 MB last-level cache, 115 / 123 / 194 ps beyond;
+//   - fused: per round 15 us for the halo planes and, per plane, a part for the workgroup and one for the share of
+//     its lanes that have nodes.
+// Two launches run where they are 3% faster by these: then no box of the 23 was slower than the fused form
+// (FP32 tau = 0.8: 64^3 31 us against 56, 80^3 64 against 78; 96^3 104 fused against 107).
+bool split_totals(const lbm_params& p, const StepGeom& fused, const StepGeom& split, int cus, int per_cu)
+{
+    if (!split_covers(p)) return false;
+    const bool mrt = p.collision == LBM_COLLISION_MRT, wide = p.storage_bytes == 8;
+    if ((p.tau == 1.0 && !mrt) || (wide && mrt)) return true;
+    struct Cost { double lane_ps[2], group_us, nodes_us, round_us; };
+    static const Cost costs[3] = {{{111, 115}, 9.35, 3.82, 14.8},   // FP32 BGK
+                                  {{115, 123}, 9.47, 4.15, 15.9},   // FP32 MRT
+                                  {{168, 194}, 8.81, 3.63, 15.1}};  // FP64 BGK
+    const Cost& c = costs[wide ? 2 : (mrt ? 1 : 0)];
+    int stx, sty, ftx, fty, unused;
+    split_tile(stx, sty);
+    step_tile(p.lattice, p.storage_bytes, 0, ftx, fty, unused);
+    const double lanes = (double)split.ntx * stx * split.nty * sty * p.nz;
+    const double two = 5.0 + 1e-6 * c.lane_ps[2 * state_bytes(p) > (256u << 20)] * lanes;
+    const long long round = (long long)cus * per_cu;
+    const long long rounds = (step_workgroups(fused) + round - 1) / round;
+    const double planes = (double)rounds * fused.chunk;
+    const double share = (double)p.nx * p.ny * p.nz / (planes * round * ftx * fty);
+    return two < 0.97 * (planes * (c.group_us + c.nodes_us * share) + rounds * c.round_us);
+}
+
 // The scratch of the two-launch step: a workspace, not state.  False without room for it.
 bool ensure_split(lbm_sim* s)
 {
@@ -943,9 +977,10 @@ lbm_status lbm_step_reduce(lbm_sim* s, int nsteps, double out[5])
     lbm_status st = enqueue_steps(s, nsteps - 1);
     if (st != LBM_OK) return st;
     // the last step's partial totals (5 per workgroup) and the totals, grown on demand
-    // without a launch chosen by the caller, the last step runs as two launches wherever they apply:
-    // their totals cost a few per cent, the fused form's a fifth (128^3: 223 us against 190)
-    const bool split = !s->launch_set && ensure_split(s);
+    int tx, ty, per_cu;
+    step_tile(s->p.lattice, s->p.storage_bytes, s->variant, tx, ty, per_cu);
+    const bool split = !s->launch_set &&
+                       split_totals(s->p, s->geom, split_geometry(s->p, s->cus), s->cus, per_cu) && ensure_split(s);
     const StepGeom& geom = split ? s->split_geom : s->geom;
     const long long wg = step_workgroups(geom);
     if (5 * wg + 8 > s->step_partials_len) {

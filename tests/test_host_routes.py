@@ -29,3 +29,42 @@ result(out)
         assert count % 2 == n % 2 and count <= n
         assert dst == where and (src == where) == (n % 2 == 0)
     assert (max(n / count for n, count, *_ in got) > 1) == several
+
+
+MRT = "collision=1, s_e=1.19, s_eps=1.4, s_q=1.2, s_m=1.98, "
+
+
+@pytest.mark.parametrize("shape,storage,kind,form", [
+    # the fused form was 8 to 16% faster
+    ("(128, 128, 128)", 4, "tau=0.8", "k_step"), ("(64, 256, 256)", 4, "tau=0.8", "k_step"),
+    ("(256, 200, 64)", 4, MRT + "tau=0.8", "k_step"), ("(112, 112, 112)", 4, MRT + "tau=0.8", "k_step"),
+    # 4 to 7%
+    ("(256, 200, 64)", 8, "tau=0.8", "k_step"), ("(64, 256, 256)", 8, "tau=0.8", "k_step"),
+    ("(300, 96, 96)", 8, "tau=0.8", "k_step"), ("(200, 200, 200)", 4, "tau=0.8", "k_step"),
+    # two launches 9 to 25%
+    ("(64, 64, 64)", 4, "tau=0.8", "k_split_moments"), ("(80, 80, 80)", 4, MRT + "tau=0.8", "k_split_moments"),
+    ("(100, 100, 100)", 8, "tau=0.8", "k_split_moments"), ("(128, 128, 128)", 8, MRT + "tau=1.0", "k_split_moments"),
+    # tau = 1 and FP64 MRT throughout
+    ("(128, 128, 128)", 4, "tau=1.0", "k_split_moments"), ("(64, 256, 256)", 4, "tau=1.0", "k_split_moments"),
+    ("(64, 256, 256)", 8, "tau=1.0", "k_split_moments"), ("(64, 256, 256)", 8, MRT + "tau=0.8", "k_split_moments"),
+    # states of 4 GB, and planes
+    ("(400, 300, 240)", 4, "tau=1.0", "k_step"), ("(1, 300, 240)", 4, "tau=1.0", "k_step"),
+])
+def test_the_step_with_totals_takes_the_faster_form(shape, storage, kind, form):
+    """The form of lbm_step_reduce's last step against what was measured; and a simulation that takes the fused form
+    there holds no scratch for the other."""
+    q = 9 if shape.startswith("(1,") else 19
+    got = hostrun.run("""
+s = case(%d, %s, %d, %s)
+held = fake.fake_held()
+launches()
+s.step_reduce(1)
+result([[k for k, *_ in launches()], fake.fake_held() - held])
+""" % (q, shape, storage, kind))
+    kernels, grown = got
+    assert kernels[0] == form
+    if form == "k_step":
+        assert kernels[:2] == ["k_step", "k_sum_partials"]
+        assert grown <= 8 * (5 * 8192 + 8)
+    else:
+        assert kernels[:3] == ["k_split_moments", "k_split_collide", "k_sum_partials"]
