@@ -452,31 +452,40 @@ hipError_t copy_to_host(lbm_pool* p, const HostCopy* copies, int count)
 // its estimated time is below the fused form's and its moments fit the workspace.
 // Fused, per kind: 20 plane iterations (chunks of 16 and 4 more) per round of kPoolGrid tiles, 9.4 us
 // each in a full round and 5 us on an idle chip (MRT a tenth more), and 5 us for k_pool_advance.
-// Two launches: 4 us and a cost per lane of the tiles.  Measured, us per step, fused and two launches:
-// 32^3 114 and 12.4, 4 x 32^3 124 and 17.5, 64^3 138 and 28, 96^3 164 and 97, 2 x 96^3 182 and 183,
-// 3 x 96^3 328 and 254, 4 x 96^3 349 and 326, 2 x 128^3 367 and 411.
+// Two launches: 4 us, 8 us for each launch that further kinds add (they run one after another, each over the whole
+// list), and a cost per lane of the tiles.  Measured, us per step, fused and two launches: 32^3 114 and 12.4,
+// 4 x 32^3 124 and 17.5, 64^3 138 and 28, 96^3 164 and 97, 2 x 96^3 182 and 183, 3 x 96^3 328 and 254, 4 x 96^3
+// 349 and 326, 2 x 128^3 367 and 411; periodic, walls and table 32^3 413 and 46, with MRT each too 879 and 100.
 bool plan_split(lbm_pool* p, const int* kind_tiles)
 {
     if (!p->workspace) return false;
     static const double lane_ps[2] = {94.0, 113.0};
     double split_us = 4.0, fused_us = 5.0;
-    long long tiles = 0;
+    long long tiles[kPoolKinds] = {};
     size_t need = 0;
     for (int s = 0; s < p->max_slots; ++s) {
         const SlotEntry& d = p->table[s];
         if (!p->slots[s].used || !d.active) continue;
         const long long t = (long long)d.split.ntx * d.split.nty * d.split.nz;
-        tiles += t;
+        tiles[d.kind] += t;
         split_us += 1e-6 * lane_ps[d.kind >= 3] * (double)(t * kSplitTX * kSplitTY);
         need += (split_scratch_bytes(4, (long long)d.geom.pitch * d.geom.ny * d.geom.nz) + kAlign - 1) / kAlign * kAlign;
     }
+    int launches = 0;   // collisions, one per kind, and moments, one per kind but for MRT
     for (int k = 0; k < kPoolKinds; ++k) {
         const int full = kind_tiles[k] / kPoolGrid, rest = kind_tiles[k] % kPoolGrid;
         fused_us += (k >= 3 ? 1.1 : 1.0) * (kPoolChunk + 4) * (9.4 * full + (rest ? 5.0 + 4.4 * rest / kPoolGrid : 0.0));
+        launches += tiles[k] > 0;
+        if (k < 3) launches += tiles[k] + tiles[k + 3] > 0;
     }
+    // with several kinds the estimates are 5% off either way (four of 120^3 823 and 872, of 96^3 720 and 419)
+    if (launches > 2) split_us = (split_us + 8.0 * (launches - 2)) / 0.95;
     if (need > p->workspace_bytes || !(split_us < fused_us)) return false;
+    // by the tiles of the kind, which are what its launch has: six kinds of 48^3 take 188 us per step with the chunks
+    // that all tiles together would get, and 161 with these
     const long long round = 3LL * kPoolGrid;
-    const int chunk = tiles <= round ? 1 : (tiles <= 16 * round ? 2 : 4);
+    int chunk[kPoolKinds];
+    for (int k = 0; k < kPoolKinds; ++k) chunk[k] = tiles[k] <= round ? 1 : (tiles[k] <= 16 * round ? 2 : 4);
     int blocks = 0, split_tiles = 0;
     size_t off = 0;
     for (int s = 0; s < p->max_slots; ++s) {
@@ -485,7 +494,7 @@ bool plan_split(lbm_pool* p, const int* kind_tiles)
         p->h_begins[p->max_slots + s] = split_tiles;
         if (!p->slots[s].used || !d.active) continue;
         StepGeom& g = d.split;
-        g.chunk = chunk < g.nz ? chunk : g.nz;
+        g.chunk = std::min(chunk[d.kind], g.nz);
         g.nchunks = (g.nz + g.chunk - 1) / g.chunk;
         d.scratch = p->workspace + off;
         off += (split_scratch_bytes(4, (long long)g.pitch * g.ny * g.nz) + kAlign - 1) / kAlign * kAlign;
@@ -562,14 +571,16 @@ lbm_status capture_graph(lbm_pool* p, int kinds)
     hipLaunchKernelGGL((k_pool_collide<EXTK == 0 ? kExtNone : (EXTK == 1 ? kExtWalls : kExtTable), MRT>), \
                        dim3(cgrid), dim3(kSplitThreads), 0, p->stream, p->d_slots, state, next, p->d_hdr, \
                        p->d_begins + p->max_slots, p->d_table, p->tab_s0, p->tab_inv_ds, p->d_errs)
+            // collisions right behind the moments they read, while those are in the last-level cache (two kinds
+            // of 120^3: 398 us per step, with the moments of both first 434)
             LBM_POOL_MOMENTS(0);
-            LBM_POOL_MOMENTS(1);
-            LBM_POOL_MOMENTS(2);
             LBM_POOL_COLLIDE(0, false);
-            LBM_POOL_COLLIDE(1, false);
-            LBM_POOL_COLLIDE(2, false);
             LBM_POOL_COLLIDE(0, true);
+            LBM_POOL_MOMENTS(1);
+            LBM_POOL_COLLIDE(1, false);
             LBM_POOL_COLLIDE(1, true);
+            LBM_POOL_MOMENTS(2);
+            LBM_POOL_COLLIDE(2, false);
             LBM_POOL_COLLIDE(2, true);
 #undef LBM_POOL_MOMENTS
 #undef LBM_POOL_COLLIDE
