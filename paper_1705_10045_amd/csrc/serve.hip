@@ -277,10 +277,11 @@ struct lbm_pool {
     bool own_stream = false;
     hipStream_t side = nullptr;              // admissions and collections
     SlotDesc* h_up = nullptr;                // pinned: the table as uploaded before a replay, and behind it
-    PoolHeader* h_hdr = nullptr;             // pinned: its header
-    SlotState* h_state = nullptr;            // the slots' state and the work list (h_begins)
-    SlotState* h_rb = nullptr;               // pinned: the state read back after a replay
-    int* h_errs = nullptr;                   // pinned: the error words read back after a replay
+    SlotState* h_state = nullptr;            // the slots' state,
+    int* h_begins = nullptr;                 // the work list of the two-launch step (as d_begins),
+    PoolHeader* h_hdr = nullptr;             // the table's header,
+    SlotState* h_rb = nullptr;               // and the state
+    int* h_errs = nullptr;                   // and error words read back after a replay
     hipEvent_t done = nullptr;               // end of the replay in flight and of its readback
     bool in_flight = false;
     std::vector<long long> launched;         // ticket in each slot when that replay was launched
@@ -298,12 +299,11 @@ struct lbm_pool {
     double* d_table = nullptr;
     double tab_s0 = 0, tab_inv_ds = 0;
     double* d_staging = nullptr;             // initial fields of a request (5 n doubles)
-    double* d_scratch = nullptr;             // moment scratch (10 n doubles)
+    double* d_scratch = nullptr;             // moment scratch and fields (8 n doubles)
     double* d_red = nullptr;                 // reduction partials (kPoolRedBlocks x 5)
     double* d_totals = nullptr;              // per slot: totals at admission, then at the end
     int* d_begins = nullptr;                 // two-launch step: first node block and tile per slot (behind d_state)
-    int* h_begins = nullptr;
-    char* h_ring = nullptr;                  // pinned: blocks that collected fields come through
+    char* h_ring = nullptr;                  // pinned: blocks that collected fields come through (ensure_ring)
     hipEvent_t ring_done[kRingThreads * kRingDepth] = {};
     char* workspace = nullptr;               // its moments (null: fused steps only)
     size_t workspace_bytes = 0;
@@ -390,18 +390,34 @@ struct HostCopy {
     size_t bytes;
 };
 
+// The pinned blocks of copy_to_host, which the pool keeps from its first long copy on.  False where there are none to be
+// had.
+bool ensure_ring(lbm_pool* p)
+{
+    if (p->h_ring) return true;
+    bool ok = true;
+    for (hipEvent_t& ev : p->ring_done)
+        ok = ok && (ev || hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess);
+    ok = ok && hipHostMalloc((void**)&p->h_ring, kRingBlock * kRingThreads * kRingDepth, hipHostMallocDefault) == hipSuccess;
+    if (ok) return true;
+    (void)hipGetLastError();
+    p->h_ring = nullptr;
+    return false;
+}
+
 // Copies device arrays to pageable host memory, behind what the side stream holds, and waits for them.
 // The runtime's own copy into pageable memory reaches 17 GB/s (96^3, 42 MB: 2.6 ms, and 4.5 ms into
 // memory that the process touches for the first time), the link 56 GB/s: the copy out of its staging
 // memory is serial.  Here every thread has blocks of its own, fills one by DMA while it empties the
 // other, and the threads share the page faults of new memory (a 96^3 request, collected beside a
-// replay: 4.5 to 2.3 ms; a 64^3 one 0.74 to 0.51).  Short copies stay with the runtime.
+// replay: 4.5 to 2.3 ms; a 64^3 one 0.74 to 0.51).  Short copies stay with the runtime, and
+// all do without the pinned blocks.
 hipError_t copy_to_host(lbm_pool* p, const HostCopy* copies, int count)
 {
     size_t total = 0;
     for (int k = 0; k < count; ++k) total += copies[k].bytes;
     const int threads = std::min(kRingThreads, host_threads((long long)total, 2 * kRingBlock));
-    if (threads < 2) {
+    if (threads < 2 || !ensure_ring(p)) {
         hipError_t e = hipSuccess;
         for (int k = 0; k < count && e == hipSuccess; ++k)
             e = hipMemcpyAsync(copies[k].dst, copies[k].src, copies[k].bytes, hipMemcpyDeviceToHost, p->side);
@@ -706,38 +722,57 @@ lbm_status lbm_pool_create(size_t hbm_budget_bytes, int max_slots, int steps_per
     const long long nmax = (long long)kPoolMaxEdge * kPoolMaxEdge * kPoolMaxEdge;
     hipError_t e = hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&p->done, hipEventDisableTiming);
-    // descriptors, state (two halves on the device) and work list of the slots in one allocation each
+    // One allocation of device memory (the arena, what a replay needs, staging, and the two-launch step's
+    // workspace) and one of pinned memory: 14 by themselves took half of the 0.5 ms of a creation and of the 1.1 ms
+    // of a release.  The workspace, an eighth of the arena, holds the moments of all that the arena can hold (36 of
+    // 304 bytes per node), and beyond 7 million nodes the fused form is as fast; without room for it the pool
+    // takes the fused form.
+    size_t end = 0;
+    const auto part = [&end](size_t bytes) {
+        const size_t at = end;
+        end += (bytes + kAlign - 1) / kAlign * kAlign;
+        return at;
+    };
+    // descriptors, state (two halves on the device) and work list of the slots lie one behind the other
     const size_t table_bytes = (sizeof(SlotDesc) + 2 * sizeof(SlotState) + 2 * sizeof(int)) * max_slots;
-    if (e == hipSuccess) e = hipHostMalloc((void**)&p->h_up, table_bytes, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&p->h_rb, sizeof(SlotState) * max_slots, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&p->h_hdr, sizeof(PoolHeader), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&p->h_errs, sizeof(int) * max_slots, hipHostMallocDefault);
-    if (e == hipSuccess)
-        e = hipHostMalloc((void**)&p->h_ring, kRingBlock * kRingThreads * kRingDepth, hipHostMallocDefault);
-    for (hipEvent_t& ev : p->ring_done)
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->arena, p->budget);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_slots, table_bytes);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_hdr, sizeof(PoolHeader));
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_errs, sizeof(int) * max_slots);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_staging, sizeof(double) * 5 * nmax);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_scratch, sizeof(double) * 10 * nmax);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_red, sizeof(double) * 5 * kPoolRedBlocks);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_totals, sizeof(double) * 10 * max_slots);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_table, sizeof(double) * 2 * kMaxwellPoints);
+    const size_t h_table = part(table_bytes), h_hdr = part(sizeof(PoolHeader));
+    const size_t h_rb = part(sizeof(SlotState) * max_slots), h_errs = part(sizeof(int) * max_slots);
+    char* host = nullptr;
+    if (e == hipSuccess) e = hipHostMalloc((void**)&host, end, hipHostMallocDefault);
+    end = 0;
+    part(p->budget);
+    const size_t d_slots = part(table_bytes), d_hdr = part(sizeof(PoolHeader)), d_errs = part(sizeof(int) * max_slots);
+    const size_t d_staging = part(sizeof(double) * 5 * nmax), d_scratch = part(sizeof(double) * 8 * nmax);
+    const size_t d_red = part(sizeof(double) * 5 * kPoolRedBlocks), d_totals = part(sizeof(double) * 10 * max_slots);
+    const size_t d_table = part(sizeof(double) * 2 * kMaxwellPoints);
+    p->workspace_bytes = std::min(p->budget / 8, (size_t)256 << 20);
+    if (e == hipSuccess) {
+        e = hipMalloc((void**)&p->arena, end + p->workspace_bytes);
+        if (e == hipSuccess) {
+            p->workspace = p->arena + end;
+        } else {
+            (void)hipGetLastError();
+            e = hipMalloc((void**)&p->arena, end);
+        }
+    }
+    p->h_up = reinterpret_cast<SlotDesc*>(host);
     if (e != hipSuccess) { lbm_status r = hip_fail(e, "pool allocation"); lbm_pool_destroy(p); return r; }
-    p->h_state = reinterpret_cast<SlotState*>(p->h_up + max_slots);
+    p->h_state = reinterpret_cast<SlotState*>(host + h_table + sizeof(SlotDesc) * max_slots);
     p->h_begins = reinterpret_cast<int*>(p->h_state + 2 * max_slots);
+    p->h_hdr = reinterpret_cast<PoolHeader*>(host + h_hdr);
+    p->h_rb = reinterpret_cast<SlotState*>(host + h_rb);
+    p->h_errs = reinterpret_cast<int*>(host + h_errs);
+    p->d_slots = reinterpret_cast<SlotDesc*>(p->arena + d_slots);
     p->d_state = reinterpret_cast<SlotState*>(p->d_slots + max_slots);
     p->d_begins = reinterpret_cast<int*>(p->d_state + 2 * max_slots);
+    p->d_hdr = reinterpret_cast<PoolHeader*>(p->arena + d_hdr);
+    p->d_errs = reinterpret_cast<int*>(p->arena + d_errs);
+    p->d_staging = reinterpret_cast<double*>(p->arena + d_staging);
+    p->d_scratch = reinterpret_cast<double*>(p->arena + d_scratch);
+    p->d_red = reinterpret_cast<double*>(p->arena + d_red);
+    p->d_totals = reinterpret_cast<double*>(p->arena + d_totals);
+    p->d_table = reinterpret_cast<double*>(p->arena + d_table);
     p->free_blocks[0] = p->budget;
-    // the two-launch step's workspace: an eighth of the arena holds the moments of all it can hold
-    // (36 of 304 bytes per node), and beyond 7 million nodes the fused form is as fast
-    p->workspace_bytes = std::min(p->budget / 8, (size_t)256 << 20);
-    if (hipMalloc((void**)&p->workspace, p->workspace_bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        p->workspace = nullptr;
-    }
     // table of the band limits, the same one every simulation uses
     std::vector<double> tab(2 * kMaxwellPoints);
     const double s_lo = std::sqrt(1.0 - kLatentTmax), s_hi = std::sqrt(1.0 - kLatentTmin);
@@ -752,10 +787,9 @@ lbm_status lbm_pool_create(size_t hbm_budget_bytes, int max_slots, int steps_per
     if (e == hipSuccess) e = hipMemsetAsync(p->d_errs, 0, sizeof(int) * max_slots, p->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
     if (e != hipSuccess) { lbm_status r = hip_fail(e, "pool setup"); lbm_pool_destroy(p); return r; }
-    // the graphs of the common kind set (periodic BGK requests only) up front
+    // the graph of the common kind set (periodic BGK requests only) up front
     lbm_status st = upload_table(p);
     if (st == LBM_OK) st = capture_graph(p, 1);
-    if (st == LBM_OK && p->workspace) st = capture_graph(p, 1 | (1 << kPoolKinds));
     if (st != LBM_OK) { lbm_pool_destroy(p); return st; }
     *out = p;
     return LBM_OK;
@@ -978,22 +1012,10 @@ lbm_status lbm_pool_destroy(lbm_pool* p)
         if (p->graph[k]) (void)hipGraphDestroy(p->graph[k]);
     }
     if (p->arena) (void)hipFree(p->arena);
-    if (p->workspace) (void)hipFree(p->workspace);
-    if (p->d_slots) (void)hipFree(p->d_slots);
-    if (p->d_hdr) (void)hipFree(p->d_hdr);
-    if (p->d_errs) (void)hipFree(p->d_errs);
-    if (p->d_staging) (void)hipFree(p->d_staging);
-    if (p->d_scratch) (void)hipFree(p->d_scratch);
-    if (p->d_red) (void)hipFree(p->d_red);
-    if (p->d_totals) (void)hipFree(p->d_totals);
-    if (p->d_table) (void)hipFree(p->d_table);
     if (p->h_up) (void)hipHostFree(p->h_up);
     if (p->h_ring) (void)hipHostFree(p->h_ring);
     for (hipEvent_t ev : p->ring_done)
         if (ev) (void)hipEventDestroy(ev);
-    if (p->h_rb) (void)hipHostFree(p->h_rb);
-    if (p->h_hdr) (void)hipHostFree(p->h_hdr);
-    if (p->h_errs) (void)hipHostFree(p->h_errs);
     if (p->done) (void)hipEventDestroy(p->done);
     if (p->side) (void)hipStreamDestroy(p->side);
     if (p->own_stream && p->stream) (void)hipStreamDestroy(p->stream);

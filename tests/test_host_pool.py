@@ -51,3 +51,41 @@ def test_form_of_loads_of_several_kinds(load, split):
         classes = len(set(k[0] for k, _ in load))
         assert steps.count("k_pool_moments") == classes and steps[0] == "k_pool_moments"
         assert "k_pool_momentsk_pool_moments" not in "".join(steps)
+
+
+def test_what_a_pool_holds_and_its_fallback_without_room_for_the_workspace():
+    """Creation is one device allocation: the budget, staging for the largest request, and a workspace of an eighth of
+    the budget; without room for the workspace the same pool runs fused steps, without room for the rest creation
+    fails and leaves nothing; destruction gives everything back."""
+    got = hostrun.run(KINDS + """
+budget, out = 1 << 30, {}
+def form():   # (the fused graph of periodic requests is captured at creation)
+    launches()
+    pool.run()
+    return ([k for k, *_ in launches()] or ["k_pool_step"])[0]
+
+m0 = fake.fake_mallocs()
+pool = lbm.Pool(budget, max_slots=16, steps_per_run=1)
+out["mallocs"], out["held"] = fake.fake_mallocs() - m0, fake.fake_held()
+request(pool, "p", 32)
+out["form"] = form()
+pool.close()
+out["left"] = fake.fake_held()
+for name, room in (("tight", out["held"] - budget // 8), ("short", out["held"] - budget // 8 - 4096)):
+    fake.fake_capacity(room)
+    try:
+        pool = lbm.Pool(budget, max_slots=16, steps_per_run=1)
+        request(pool, "p", 32)
+        out[name] = [form(), fake.fake_held() <= room]
+        pool.close()
+    except lbm.LbmError as e:
+        out[name] = e.status
+    out[name + " left"] = fake.fake_held()
+result(out)
+""")
+    staging = (5 + 8) * 8 * 128 ** 3
+    assert got["mallocs"] == 1
+    assert (1 << 30) * 9 // 8 + staging <= got["held"] <= (1 << 30) * 9 // 8 + staging + (1 << 20)
+    assert got["form"] == "k_pool_moments" and got["left"] == 0
+    assert got["tight"] == ["k_pool_step", True] and got["tight left"] == 0
+    assert got["short"] == -2 and got["short left"] == 0
