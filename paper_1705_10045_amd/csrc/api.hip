@@ -564,13 +564,12 @@ MultiGeom multi_geometry(const lbm_params& p, int tx, int ty, int steps)
 }
 
 // Tiles and steps per launch of the D2Q9 boxes that take several steps per launch; steps = 0 for
-// the others.  The tiles have to run in one round, one workgroup per CU (its LDS is up to 129 KB),
-// which boxes up to about 256^2 and rows up to 10^5 nodes do: a second round already costs more
-// than single steps (300^2 FP64: 10.3 us per step against 9.3).  Among those, the tile and the
-// step count of least time per step, a launch taking about 2 us and each of its steps 2.1 us
-// plus 0.21 us per further wavefront of the region (measured over 12 tiles and 1 to 16 steps).
-// FP64 times per step: 1000 nodes 6.2 -> 2.2 us, 128^2 7.2 -> 4.4 us, 256^2 7.9 -> 6.1 us; 300^2 8.6
-// against 9.1 for single steps, but 350^2 11.1 against 10.2 (FP32 7.9 against 8.6).
+// the others.  The tiles have to run in one round, one workgroup per CU (its LDS is up to 129 KB): a region of 704
+// nodes, tile and halo, allows that up to about 350^2 and 150,000 nodes in a row.  Among the tiles and step counts
+// that do, the one of least time per step is taken, a launch taking about 2 us and each of its steps 2.1 us
+// plus 0.21 us per further wavefront of the region (measured over 12 tiles and 1 to 16 steps).  us per step, single
+// steps and these: FP64 1000 nodes 6.1 and 2.1, 128^2 7.1 and 4.5, 256^2 7.9 and 6.1, 300^2 9.3 and 8.5; FP32 256^2 7.4
+// and 5.6, 350^2 8.5 and 7.8.
 MultiGeom plan_multi(const lbm_params& p, int cus)
 {
     MultiGeom best{};
@@ -594,8 +593,15 @@ MultiGeom plan_multi(const lbm_params& p, int cus)
             }
         }
     }
-    // regions of one step beyond 9 wavefronts: single steps are as fast for FP64 populations
-    if (best.steps == 1 && p.storage_bytes == 8 && best.rx * best.ry > 576) return MultiGeom{};
+    // FP64 populations, one step: beyond 9 wavefronts single steps are as fast (350^2 10.2 us either way), and with 9
+    // where the tile is narrow, so that its rows are parts of a few lines (20 x 20: 320^2 9.6 us against 9.3,
+    // 500x200 10.2 against 9.7; 28 x 14: 304x320 8.6 against 9.1), unless the 32 x 8 tiles of single steps
+    // leave more lanes idle (40x2400 8.7 against 11.1)
+    if (best.steps == 1 && p.storage_bytes == 8) {
+        const int region = best.rx * best.ry;
+        const double lanes = ((p.nx + 31LL) / 32 * 32) * (double)((p.ny + 7LL) / 8 * 8);
+        if (region > 576 || (region > 512 && best.tx < 24 && (double)p.nx * p.ny > 0.85 * lanes)) return MultiGeom{};
+    }
     return best;
 }
 

@@ -68,3 +68,22 @@ result([[k for k, *_ in launches()], fake.fake_held() - held])
         assert grown <= 8 * (5 * 8192 + 8)
     else:
         assert kernels[:3] == ["k_split_moments", "k_split_collide", "k_sum_partials"]
+
+
+@pytest.mark.parametrize("shape,storage,form", [
+    # single steps were 3 to 11% faster
+    ("(1, 320, 320)", 8, "k_step"), ("(1, 200, 500)", 8, "k_step"), ("(1, 316, 310)", 8, "k_step"),
+    ("(1, 208, 480)", 8, "k_step"), ("(1, 450, 220)", 8, "k_step"), ("(1, 360, 360)", 8, "k_step"),
+    ("(1, 360, 360)", 4, "k_step"),
+    # the other form 5 to 21%
+    ("(1, 300, 300)", 8, "k_multi_step"), ("(1, 320, 304)", 8, "k_multi_step"), ("(1, 2400, 40)", 8, "k_multi_step"),
+    ("(1, 320, 320)", 4, "k_multi_step"), ("(1, 350, 350)", 4, "k_multi_step"),
+])
+def test_plane_steps_take_the_faster_form(shape, storage, form):
+    got = hostrun.run("""
+s = case(9, %s, %d)
+launches()
+s.step_async(2)
+result([k for k, *_ in launches()])
+""" % (shape, storage))
+    assert len(set(got)) == 1 and got[0].startswith(form)   # (k_step, or k_step_waves)
