@@ -166,17 +166,19 @@ lbm_status lbm_check(lbm_sim* sim);
  * u* = (sum c_k N_k + F/2)/rho (eq:ustar) with F the force of section 3 plus the body force
  * rho g, T = E/(rho c_v).  With walls, the populations pulled from beyond a wall are the
  * bounced-back ones, as in the step.  Each argument is a caller-owned host FP64 array of n
- * values (u_star: 3n), or NULL to skip it.  Synchronises. */
+ * values (u_star: 3n), or NULL to skip it.  Allocates nothing.  Synchronises. */
 lbm_status lbm_moments(lbm_sim* sim, double* rho, double* u_star, double* E, double* T);
 
 /* Same as lbm_moments but into caller-owned device FP64 arrays on the simulation's device;
- * enqueued on the simulation's stream (not synchronised).  The first call allocates a moment
- * scratch of 10 n doubles that the simulation keeps until lbm_free. */
+ * enqueued on the simulation's stream (not synchronised).  u_star is right also where the other
+ * outputs share an array, which then holds one of them or a mixture.  The first call allocates a
+ * moment scratch of 2 n doubles that the simulation keeps until lbm_free, unless it holds the
+ * workspace of the two-launch step (lbm_footprint_bytes), which serves. */
 lbm_status lbm_moments_device(lbm_sim* sim, double* rho, double* u_star, double* E, double* T);
 
 /* lbm_moments_device for callers that cannot allocate device memory (code under stream
  * capture, tight serving loops, harnesses that forbid the allocator).  Same kernels and the
- * same results, bit for bit, but the scratch (7 n doubles) is a fixed 128 MiB device array of
+ * same results, bit for bit, but the scratch (2 n doubles) is a fixed 37 MiB device array of
  * the library, so the call allocates and frees nothing.  Limit: boxes of at most 2,396,745
  * nodes (128^3 fits); LBM_EINVAL for larger ones.  Outputs: caller-owned device FP64 arrays of
  * n values (u_star: 3n) on the simulation's device, any may be NULL; enqueued on the
@@ -216,8 +218,11 @@ lbm_status lbm_step_reduce(lbm_sim* sim, int nsteps, double out[5]);
 /* Number of time steps taken since lbm_init (or restored by lbm_restore). */
 long long lbm_step_count(const lbm_sim* sim);
 
-/* Bytes of device memory the state of a simulation with these parameters occupies
- * (population buffers; excludes transient buffers of lbm_moments). */
+/* Bytes of device memory the state of a simulation with these parameters occupies: population
+ * buffers and tables.  Beside it a simulation holds up to 4 MB of rounding and, for D3Q19 states
+ * under 4 GB whose step runs as two launches (from the start, or in lbm_step_reduce), a workspace of
+ * 36 (FP32) or 56 (FP64) bytes per node of the x rows padded to 128 bytes: 9 to 12% more.  Without room
+ * for the workspace the other form of the step runs, with the same results. */
 size_t lbm_footprint_bytes(const lbm_params* params);
 
 /* Serialise the complete state (populations, step count) into host_buf of capacity cap;

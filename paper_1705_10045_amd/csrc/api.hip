@@ -539,6 +539,7 @@ bool ensure_split(lbm_sim* s)
 {
     if (s->d_split) return true;
     if (!split_covers(s->p)) return false;
+    if (s->split_refused) return false;
     s->split_geom = split_geometry(s->p, s->cus);
     if (hipMalloc(&s->d_split, split_scratch_bytes(s->p.storage_bytes, plane_elements(s->p))) == hipSuccess) {
         s->own_split = true;
@@ -546,6 +547,7 @@ bool ensure_split(lbm_sim* s)
     }
     (void)hipGetLastError();
     s->d_split = nullptr;
+    s->split_refused = true;   // (a refusal costs more than a step gains)
     return false;
 }
 
@@ -621,12 +623,15 @@ hipError_t enqueue_multi(lbm_sim* s, int steps)
 // 105 and 330 us, six by themselves took 195 and 780, beside 2.5 ms for 100 steps.
 hipError_t allocate(lbm_sim* s)
 {
-    constexpr size_t kPageBytes = (size_t)2 << 20;   // the second buffer begins on a large page as the first
     int tx, ty, per_cu;
     step_tile(s->p.lattice, s->p.storage_bytes, s->variant, tx, ty, per_cu);
     const StepGeom geom = split_geometry(s->p, s->cus);
     const auto part = [](size_t bytes) { return (bytes + 4095) / 4096 * 4096; };
-    const size_t state = (state_bytes(s->p) + kPageBytes - 1) / kPageBytes * kPageBytes;
+    // the second buffer begins on a large page as the first, but for states of a few pages, which would
+    // hold up to ten times their size (1000 nodes 4.3 MB for 0.4)
+    constexpr size_t kLargePage = (size_t)2 << 20;
+    const size_t bytes = state_bytes(s->p);
+    const size_t state = bytes < 8 * kLargePage ? part(bytes) : (bytes + kLargePage - 1) / kLargePage * kLargePage;
     const size_t err = 2 * state, table = err + part(sizeof(int) * 16);
     const size_t partials = table + part(sizeof(double) * maxwell_table().rho.size());
     const size_t scratch = partials + part(sizeof(double) * (5 * s->red_blocks + 8));
@@ -912,11 +917,16 @@ lbm_status lbm_launch_info(const lbm_sim* s, int info[4])
     return LBM_OK;
 }
 
-static lbm_status ensure_scratch(lbm_sim* s)
+// Scratch of the moment kernels, rho and Phi: that of the two-launch step where there is one (36 bytes per node
+// at least, and nothing in it outlives a step), else an allocation that the simulation keeps.
+static lbm_status moment_scratch(lbm_sim* s, double** scratch)
 {
-    if (s->d_scratch) return LBM_OK;
-    hipError_t e = hipMalloc((void**)&s->d_scratch, sizeof(double) * 10 * s->n);
-    if (e != hipSuccess) return hip_fail(e, "hipMalloc(moment scratch)");
+    if (s->d_split) { *scratch = static_cast<double*>(s->d_split); return LBM_OK; }
+    if (!s->d_scratch) {
+        hipError_t e = hipMalloc((void**)&s->d_scratch, sizeof(double) * 2 * s->n);
+        if (e != hipSuccess) return hip_fail(e, "hipMalloc(moment scratch)");
+    }
+    *scratch = s->d_scratch;
     return LBM_OK;
 }
 
@@ -925,9 +935,10 @@ lbm_status lbm_moments_device(lbm_sim* s, double* rho, double* u_star, double* E
     clear_error();
     if (!s) { set_error("simulation is NULL"); return LBM_EINVAL; }
     if (lbm_status sd = use_device(s->device); sd != LBM_OK) return sd;
-    lbm_status st = ensure_scratch(s);
+    double* scratch = nullptr;
+    lbm_status st = moment_scratch(s, &scratch);
     if (st != LBM_OK) return st;
-    hipError_t e = launch_moments(s->p.lattice, s->p.storage_bytes, s->buf[s->cur], s->d_scratch, s->p.nx,
+    hipError_t e = launch_moments(s->p.lattice, s->p.storage_bytes, s->buf[s->cur], scratch, s->p.nx,
                                   s->p.ny, s->p.nz, s->geom.pitch, s->plane, s->phys, s->aux.eos_p, s->d_err, rho,
                                   u_star, E, T, s->stream);
     if (e != hipSuccess) return hip_fail(e, "moments launch");
@@ -939,11 +950,10 @@ lbm_status lbm_moments(lbm_sim* s, double* rho, double* u_star, double* E, doubl
     clear_error();
     if (!s) { set_error("simulation is NULL"); return LBM_EINVAL; }
     if (lbm_status sd = use_device(s->device); sd != LBM_OK) return sd;
-    lbm_status st = ensure_scratch(s);
-    if (st != LBM_OK) return st;
     const long long n = s->n;
-    double* scr = s->d_scratch;
-    // behind the two fields of the moment kernels' own scratch
+    // scratch and fields (64 B per node) pass through the population buffer that the next step writes (72 B per
+    // node at least); its padding is cleared again for that
+    double* scr = static_cast<double*>(s->buf[1 - s->cur]);
     double *d_rho = scr + 2 * n, *d_us = scr + 3 * n, *d_E = scr + 6 * n, *d_T = scr + 7 * n;
     hipError_t e = launch_moments(s->p.lattice, s->p.storage_bytes, s->buf[s->cur], scr, s->p.nx, s->p.ny,
                                   s->p.nz, s->geom.pitch, s->plane, s->phys, s->aux.eos_p, s->d_err, rho ? d_rho : nullptr,
@@ -952,6 +962,7 @@ lbm_status lbm_moments(lbm_sim* s, double* rho, double* u_star, double* E, doubl
     if (e == hipSuccess && u_star) e = hipMemcpyAsync(u_star, d_us, sizeof(double) * 3 * n, hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess && E) e = hipMemcpyAsync(E, d_E, sizeof(double) * n, hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess && T) e = hipMemcpyAsync(T, d_T, sizeof(double) * n, hipMemcpyDeviceToHost, s->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(s->buf[1 - s->cur], 0, state_bytes(s->p), s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return hip_fail(e, "moments");
     return read_error_word(s);

@@ -17,9 +17,9 @@
 namespace lbm {
 namespace {
 
-constexpr size_t kStaticScratchBytes = size_t(128) << 20;
-// 7 doubles per node (the moment kernels use two of them, for rho and Phi)
-constexpr long long kNoallocMaxNodes = (long long)(kStaticScratchBytes / (7 * sizeof(double)));
+// 128^3 fits.  2 doubles per node, rho and Phi.
+constexpr long long kNoallocMaxNodes = 2396745;
+constexpr size_t kStaticScratchBytes = kNoallocMaxNodes * 2 * sizeof(double);
 
 static __device__ __align__(256) double scratch[kStaticScratchBytes / sizeof(double)];
 

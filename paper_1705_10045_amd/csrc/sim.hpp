@@ -26,7 +26,7 @@ struct lbm_sim {
     double* d_partials = nullptr;        // partial sums of lbm_reduce
     double* d_step_partials = nullptr;   // per-workgroup totals of lbm_step_reduce's last step
     long long step_partials_len = 0;     // doubles held by d_step_partials
-    double* d_scratch = nullptr;         // moment scratch and fields (10n doubles), allocated on first use
+    double* d_scratch = nullptr;         // moment scratch (2n doubles) without d_split, allocated on first use
     double* d_eos_p = nullptr;           // tabulated EOS: reduced pressures and band per row
     double* d_eos_coex = nullptr;
     int red_blocks = 1;
@@ -37,6 +37,7 @@ struct lbm_sim {
     lbm::StepGeom split_geom;            // tiles and z chunks of their collision launch
     void* d_split = nullptr;             // their moment scratch
     bool own_split = false;              // allocated after the start, by itself
+    bool split_refused = false;          // there was no room for that
     lbm::MultiGeom multi{};              // D2Q9: steps taken per launch (0: single steps) and their tiles
 };
 

@@ -87,3 +87,92 @@ s.step_async(2)
 result([k for k, *_ in launches()])
 """ % (shape, storage))
     assert len(set(got)) == 1 and got[0].startswith(form)   # (k_step, or k_step_waves)
+
+
+MEMORY = """
+def held(Q, shape, storage, **kw):
+    # bytes beyond the footprint after creation, then what moments on the host, moments on the device and a step with
+    # totals add
+    s = case(Q, shape, storage, **kw)
+    out = [fake.fake_held() - lbm.lbm_footprint_bytes(s.params)]
+    for use in (s.moments, lambda: lbm.lbm_moments_device(s.handle, 256, 512, 768, 1024), lambda: s.step_reduce(1)):
+        before = fake.fake_held()
+        use()
+        out.append(fake.fake_held() - before)
+    s.close()
+    return out + [fake.fake_held()]
+"""
+
+
+@pytest.mark.parametrize("q,shape,storage,kw,split", [
+    (9, (1, 1, 1000), 8, "", 0), (9, (1, 128, 128), 8, "", 0), (9, (1, 600, 600), 4, "", 0),
+    (19, (32, 32, 32), 4, "", 36), (19, (75, 52, 41), 8, "tau=0.8", 56), (19, (128, 128, 128), 4, "tau=0.8", 0),
+])
+def test_device_memory_of_a_simulation(q, shape, storage, kw, split):
+    """Beside its footprint a simulation holds some rounding (none to speak of for a small state) and, where its steps
+    are two launches, their workspace; moments add 16 bytes per node where there is no workspace."""
+    n = shape[0] * shape[1] * shape[2]
+    pitch = -(-shape[2] * storage // 128) * 128 // storage
+    extra, host, device, totals, left = hostrun.run(MEMORY + "result(held(%d, %r, %d, %s))" % (q, shape, storage, kw))
+    state = 4 * q * storage * n
+    work = split * pitch * shape[0] * shape[1]
+    assert work <= extra <= work + (65536 if state < 16 << 20 else 4 << 20) + 40 * (1024 + 8)
+    assert host == 0
+    assert device == (0 if split else 16 * n)
+    assert totals <= 8 * (5 * 8192 + 8)
+    assert left == 0
+
+
+def test_steps_without_room_for_the_workspace():
+    """No room for the workspace at creation: the fused step; none for the step with totals: its fused form, and the
+    runtime is asked once only."""
+    got = hostrun.run("""
+out = []
+for shape, kw in (((32, 32, 32), {}), ((128, 128, 128), {})):
+    s = case(19, shape, 4, **kw)
+    held = fake.fake_held()
+    need = 36 * shape[0] * shape[1] * shape[2]
+    s.close()
+    # the box whose steps are two launches has its workspace inside what it holds, the other not
+    fake.fake_capacity(held + 4096 - (need if shape[0] == 32 else 0) + 8 * (5 * 8192 + 8))
+    s = case(19, shape, 4, **kw)
+    launches()
+    s.step_async(1)
+    forms = [launches()[0][0]]
+    calls = []
+    for i in range(3):
+        m = fake.fake_mallocs()
+        s.step_reduce(1)
+        calls.append(fake.fake_mallocs() - m)
+    forms += [k for k, *_ in launches()][:2]
+    s.moments()
+    out.append([forms, calls])
+    s.close()
+    fake.fake_capacity((1 << 64) - 1)
+result(out)
+""")
+    for forms, calls in got:
+        assert forms == ["k_step", "k_step", "k_sum_partials"]
+        assert calls == [2, 0, 0]     # the workspace refused, the totals' partial sums
+
+
+def test_moments_clear_the_buffer_they_pass_through():
+    """lbm_moments takes the population buffer of the next step for its fields, and clears it."""
+    got = hostrun.run("""
+out = []
+for args in ((9, (1, 20, 31), 4), (19, (5, 9, 33), 8)):
+    s = case(*args)
+    for steps in (1, 2):
+        launches()
+        s.step_async(steps)
+        last = launches()[-1]
+        s.moments()
+        seen = launches()
+        out.append([last[3], seen[0][2], [x for x in seen if x[0] == "memset"],
+                    (lbm.lbm_footprint_bytes(s.params) - 16 * 4096 - 64) // 2])
+    s.close()
+result(out)
+""")
+    for state, read, cleared, size in got:
+        assert read == state
+        assert len(cleared) == 1 and cleared[0][1] == size and cleared[0][2] != state
