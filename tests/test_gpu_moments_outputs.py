@@ -1,5 +1,7 @@
 """lbm_moments_device and its allocation-free form where outputs the caller does not want share an array:
 u* is what separate arrays give, bit for bit, on both lattices and storages and between walls."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -24,10 +26,18 @@ def test_u_star_beside_one_array_for_the_other_fields(entry, name):
     with lbm.Sim(case["Q"], case["params"], case["rho0"], case["u0"], case["T0"], storage_bytes=storage) as s:
         s.step(5)
         want = s.moments()["u_star"].ravel()
-        waste, u = DeviceArray(n), DeviceArray(3 * n)
+        waste, half, u = DeviceArray(n), DeviceArray(2 * n), DeviceArray(3 * n)
         for given in ((waste, waste, waste), (waste, None, waste), (waste, waste, None), (None, waste, waste)):
             rho, E, T = (None if w is None else w.ptr for w in given)
             entry(s.handle, rho, u.ptr, E, T)
+            s.check()
+            np.testing.assert_array_equal(u.numpy(), want)
+        # arrays that overlap by part
+        for shift in (1, n // 2, n - 1):
+            entry(s.handle, half.ptr, u.ptr, None, ctypes.c_void_p(half.ptr.value + 8 * shift))
+            s.check()
+            np.testing.assert_array_equal(u.numpy(), want)
+            entry(s.handle, ctypes.c_void_p(half.ptr.value + 8 * shift), u.ptr, half.ptr, None)
             s.check()
             np.testing.assert_array_equal(u.numpy(), want)
         # the density in the first component's place: u* is written last
@@ -35,6 +45,7 @@ def test_u_star_beside_one_array_for_the_other_fields(entry, name):
         s.check()
         np.testing.assert_array_equal(u.numpy(), want)
         waste.free()
+        half.free()
         u.free()
 
 
