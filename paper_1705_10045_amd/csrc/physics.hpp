@@ -105,12 +105,12 @@ __host__ __device__ inline bool table_band(double Tr, const Phys& p,
 
 // Position of reduced temperature Tr on the Maxwell table (nodes uniform in s = sqrt(1 - Tr)):
 // the cell's node j and the offset t from it, clamped so that nodes j - 1 .. j + 2 exist whatever
-// Tr is.  False outside [kLatentTmin, kLatentTmax), where there is no band.
-__device__ __forceinline__ bool band_cell(double Tr, double s0, double inv_ds, int& j, double& t)
+// Tr is (before the conversion, which is defined for values an int can hold; Tr > 1 gives NaN and the
+// first cell).  False outside [kLatentTmin, kLatentTmax), where there is no band.
+__host__ __device__ __forceinline__ bool band_cell(double Tr, double s0, double inv_ds, int& j, double& t)
 {
     const double d = sqrt(1.0 - Tr) - s0;
-    j = (int)(d * inv_ds);
-    j = j < 1 ? 1 : (j > kMaxwellPoints - 3 ? kMaxwellPoints - 3 : j);
+    j = (int)fmin(fmax(d * inv_ds, 1.0), double(kMaxwellPoints - 3));
     t = fma(inv_ds, d, -double(j));
     return Tr >= kLatentTmin && Tr < kLatentTmax;
 }
@@ -135,10 +135,12 @@ __device__ __forceinline__ bool band_limits(double Tr, const double* __restrict_
                                             double& r1, double& r2)
 {
     if (!(Tr >= kLatentTmin && Tr < kLatentTmax)) return false;
-    int j;
-    double t;
-    band_cell(Tr, s0, inv_ds, j, t);
-    band_eval(t, tab + 2 * (j - 1), rho_c, r1, r2);
+    // as band_cell, but on the table: integer clamps, with which the fused step holds more in registers (256^3
+    // 1344 us against 1385)
+    const double d = sqrt(1.0 - Tr) - s0;
+    int j = (int)(d * inv_ds);
+    j = j < 1 ? 1 : (j > kMaxwellPoints - 3 ? kMaxwellPoints - 3 : j);
+    band_eval(fma(inv_ds, d, -double(j)), tab + 2 * (j - 1), rho_c, r1, r2);
     return true;
 }
 
