@@ -59,3 +59,21 @@ def test_a_node_that_leaves_the_domain_is_reported():
         with pytest.raises(lbm.LbmError) as e:
             s.step(400)
         assert e.value.status == lbm.LBM_EUNSTABLE
+
+
+TERMS = {"none": 0, "work": I.WORK, "conduction": I.CONDUCTION, "latent": I.LATENT, "pseudoforce": I.PSEUDOFORCE,
+         "latent at T0": I.LATENT | I.BAROTROPIC, "barotropic": I.ALL_TERMS | I.BAROTROPIC}
+
+
+@pytest.mark.parametrize("storage", [4, 8])
+@pytest.mark.parametrize("terms", sorted(TERMS))
+def test_single_terms_and_temperatures_beyond_the_band(terms, storage):
+    """Each term by itself and the barotropic pressure, with gas below the latent band's range on one side and
+    supercritical on the other."""
+    params, rho, u, T = _box(45, 70, "tau1")
+    params = dict(params, flags=TERMS[terms], T0_baro=0.85)
+    x = np.arange(70)
+    T[:] = np.where(x < 10, 0.38, np.where(x > 60, 1.2, T))
+    rho[:, :, (x < 10) | (x > 60)] = 0.05
+    print("several steps per launch: %s %dB" % (terms, storage), flush=True)
+    _compare((params, rho, u, T), storage, (1, 2, 7))

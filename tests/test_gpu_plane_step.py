@@ -59,3 +59,21 @@ def test_forms_match_bitwise_with_a_table(n, kind, storage):
         b.set_launch(2, 0)
         assert _step(a, 3) == _step(b, 3) == lbm.LBM_OK
         assert a.checkpoint() == b.checkpoint()
+
+
+@pytest.mark.parametrize("storage", [4, 8])
+@pytest.mark.parametrize("kind", sorted(KINDS))
+@pytest.mark.parametrize("nx,ny", [(512, 256), (513, 255), (512, 385), (511, 377), (512, 513), (1025, 491)])
+def test_forms_match_bitwise_with_a_table_at_the_lines(nx, ny, kind, storage):
+    """The table on a slab that stays in its domain, on the boxes at the lines where the form changes."""
+    n = max(nx, ny)
+    case = I.slab_2d(n=n, width=n // 3, params=I.physics(**KINDS[kind]))
+    args = (9, dict(case["params"], eos_table=vdw_table()), case["rho0"][:, :ny, :nx].copy(),
+            case["u0"][:, :, :ny, :nx].copy(), case["T0"][:, :ny, :nx].copy())
+    print("plane step: slab %dx%d table %s %dB" % (nx, ny, kind, storage), flush=True)
+    with lbm.Sim(*args, storage_bytes=storage) as a, lbm.Sim(*args, storage_bytes=storage) as b:
+        a.set_launch(0, 0)
+        b.set_launch(2, 0)
+        assert _step(a, 3) == _step(b, 3) == lbm.LBM_OK
+        same = a.checkpoint() == b.checkpoint()
+        assert same

@@ -63,3 +63,35 @@ def test_load_passing_from_the_fused_form_to_two_launches():
     cases = [_case("drop", (128, 128, 128), {}), _case("drop", (128, 128, 127), {}), _case("drop", (33, 48, 65), {})]
     print("draining pool", flush=True)
     _check(cases, [4, 4, 15], 4)
+
+
+def _tall(scene, nz, kw, ny=9):
+    """A box of 33 x ny nodes a plane, 2 x ceil(ny / 8) tiles."""
+    return _case(scene, (nz, ny, 33), kw)
+
+
+def test_every_kind_on_chunks_of_two():
+    """Twelve requests, 828 or 840 tiles of each kind, more than a launch has workgroups: chunks of 2 planes,
+    workgroups that go on to a second tile of another request, requests that end within a replay."""
+    kinds = [("drop", {}), ("boil", {}), ("table", {}), ("drop", dict(tau=0.8, **MRT)), ("boil", dict(tau=0.8, **MRT)),
+             ("table", dict(tau=0.8, **MRT))]
+    cases = [_tall(scene, nz, kw) for nz in (127, 80) for scene, kw in kinds]
+    cases[6] = _tall("drop", 83, dict(tau=0.8))
+    print("pool of every kind, chunks of 2", flush=True)
+    _check(cases, [7, 9, 5, 8, 6, 10, 9, 4, 7, 5, 8, 3], 4)
+
+
+def test_one_kind_on_chunks_of_four():
+    """Twelve requests of 15180 tiles: chunks of 4 planes, with up to three left over."""
+    cases = [_tall("drop", nz, kw, ny=33) for nz, kw in zip((125, 126, 127, 128) * 3, ({}, {}, dict(tau=0.8)) * 4)]
+    print("pool, chunks of 4", flush=True)
+    _check(cases, [3, 5, 4, 6, 5, 3, 4, 5, 6, 3, 4, 5], 3)
+
+
+@pytest.mark.parametrize("kind", ["walls", "table", "mrt"])
+def test_other_kinds_on_chunks_of_four(kind):
+    scene = {"walls": "boil", "table": "table", "mrt": "drop"}[kind]
+    kw = dict(tau=0.8, **MRT) if kind == "mrt" else {}
+    cases = [_tall(scene, nz, kw, ny=33) for nz in (125, 126, 127, 128) * 3]
+    print("pool, chunks of 4, %s" % kind, flush=True)
+    _check(cases, [3, 5, 4, 6, 5, 3, 4, 5, 6, 3, 4, 5], 3)

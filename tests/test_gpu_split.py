@@ -57,3 +57,35 @@ def test_two_launches_on_longer_chunks(scene, shape):
     """Chunks of 2 planes (odd height), and of 4 with one plane left over."""
     print("two launches: %s %s" % (scene, shape), flush=True)
     _both(_case(scene, shape, "tau1"), 4, 3)
+
+
+# Chunks of 2 planes (788 and 524 tiles) and of 4 (6158 and 4102), at heights that leave one and three planes over, in
+# boxes whose steps run as two launches with every collision, with totals too (checked on the CPU).
+CHUNKED = [(4, (197, 9, 33)), (4, (3079, 8, 33)), (8, (131, 9, 33)), (8, (2051, 8, 63))]
+
+
+@pytest.mark.parametrize("storage,shape", CHUNKED)
+@pytest.mark.parametrize("scene,kind", [("drop", "tau1"), ("drop", "tau"), ("drop", "mrt"), ("boil", "tau1"), ("boil", "tau"),
+                                        ("boil", "mrt"), ("table", "tau1"), ("table", "tau"), ("table", "mrt")])
+def test_every_form_on_chunks_of_two_and_four(scene, kind, storage, shape):
+    print("two launches on chunks: %s %s %s %dB" % (scene, kind, shape, storage), flush=True)
+    _both(_case(scene, shape, kind), storage, 3)
+
+
+TERMS = {"none": 0, "work": I.WORK, "conduction": I.CONDUCTION, "latent": I.LATENT, "pseudoforce": I.PSEUDOFORCE,
+         "latent at T0": I.LATENT | I.BAROTROPIC, "barotropic": I.ALL_TERMS | I.BAROTROPIC}
+
+
+@pytest.mark.parametrize("storage", [4, 8])
+@pytest.mark.parametrize("terms", sorted(TERMS))
+def test_single_terms_and_temperatures_beyond_the_band(terms, storage):
+    """Each term by itself and the barotropic pressure, on a drop in a gas that is below the latent band's range
+    on one side and supercritical on the other."""
+    shape = (11, 18, 47)
+    case = I.droplet_3d(shape=shape, radius=4.0, params=I.physics(flags=TERMS[terms], T0_baro=0.85),
+                        velocity=(0.03, -0.02, 0.01))
+    x = np.arange(shape[2])
+    case["T0"][:] = np.where(x < 8, 0.38, np.where(x > 38, 1.2, case["T0"]))
+    case["rho0"][:, :, (x < 8) | (x > 38)] = 0.05
+    print("two launches: %s %dB" % (terms, storage), flush=True)
+    _both(case, storage, 4)

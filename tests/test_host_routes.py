@@ -176,3 +176,20 @@ result(out)
     for state, read, cleared, size in got:
         assert read == state
         assert len(cleared) == 1 and cleared[0][1] == size and cleared[0][2] != state
+
+
+@pytest.mark.parametrize("kind", ["tau=1.0", "tau=0.8", MRT + "tau=0.8"])
+@pytest.mark.parametrize("storage,shape,tiles,chunk", [(4, (197, 9, 33), 4, 2), (4, (3079, 8, 33), 2, 4),
+                                                       (8, (131, 9, 33), 4, 2), (8, (2051, 8, 63), 2, 4)])
+def test_boxes_whose_two_launches_march_through_chunks(storage, shape, tiles, chunk, kind):
+    """The boxes of the GPU test of chunks run what it is there for."""
+    got = hostrun.run("""
+s = case(19, %r, %d, %s)
+launches()
+s.step_async(1)
+s.step_reduce(1)
+result([x[:2] for x in launches()])
+""" % (shape, storage, kind))
+    collide = ["k_split_collide", tiles * -(-shape[0] // chunk)]
+    assert [x[0] for x in got] == ["k_split_moments", "k_split_collide"] * 2 + ["k_sum_partials"]
+    assert got[1] == got[3] == collide
