@@ -79,6 +79,15 @@ ORACLE_BYTES_PER_NODE = 4 * 19 * 8 + 24 * 8 + 3 * 6 * 8
 HOST_CAP_BYTES = 200e9
 
 
+def step_form(case, storage, args):
+    """The step that was timed: the fused kernel where a launch was asked for or the state is 4 GB
+    and more, else the form lbm_init takes for the box."""
+    fused = (args.variant is not None or args.chunk or
+             2 * case["Q"] * storage * case["rho0"].size >= 1 << 32)
+    return ("lbm::k_step<%d,%s> (one launch per step)" % (case["Q"], "float" if storage == 4 else "double")
+            if fused else "the form of the step that lbm_init takes for this box")
+
+
 def host_available_bytes():
     """MemAvailable of the host, in bytes (0 if unknown)."""
     try:
@@ -520,8 +529,7 @@ def main():
                                           if traffic else None),
                      "copy_ceiling_GB_per_s": copy_ceiling_gbs(case["Q"], storage,
                                                                case["rho0"].shape),
-                     "kernel": "lbm::k_step<%d,%s> (one launch per step)" %
-                               (case["Q"], "float" if storage == 4 else "double"),
+                     "kernel": step_form(case, storage, args),
                      "algorithmic_bytes_per_launch": bytes_alg},
         "totals_fp64": [float(x) for x in totals],
     }

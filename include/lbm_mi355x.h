@@ -243,8 +243,9 @@ const char* lbm_last_error(void);
  * kernels by default (see lbm_set_launch), which this does not describe. */
 lbm_status lbm_launch_info(const lbm_sim* sim, int info[4]);
 
-/* The launch lbm_init chooses for these parameters (default variant, automatic z chunk) on a
- * device with `cus` compute units (256 on MI355X), in the layout of lbm_launch_info.  Host
+/* The fused launch that lbm_init plans for these parameters (default variant, automatic z chunk) on
+ * a device with `cus` compute units (256 on MI355X), in the layout of lbm_launch_info, whether or
+ * not another form of the step runs by default (lbm_set_launch).  Host
  * arithmetic only: touches no device and validates only the lattice, storage and shape
  * (LBM_EINVAL otherwise).  The z chunk minimises the number of rounds of resident workgroups
  * times (chunk + 4) planes, the moment stage's halo planes included. */

@@ -238,7 +238,9 @@ __device__ __forceinline__ R dot_c(int k, R x, R y, R z, F last)
 // The moving directions are produced pair by pair of opposite directions (P_k and P_-k share
 // the even part of the polynomial); the rest populations close the mass and energy balances in
 // FP64 over the values actually stored (the BGK, EDM and pseudoforce increments sum to zero and
-// dg(1) sums to dE), so rounding of the lattice weights cannot create mass or energy.
+// dg(1) sums to dE), so rounding of the lattice weights cannot create mass or energy.  (For FP64
+// storage and tau = 1 the sum takes the products before their own rounding, which leaves the balance
+// to that rounding, 1e-16 of a population.)
 // With MRT (which re-reads N_k like any tau != 1) the moving N'_k also lose
 // sum_i am_i M_ik / |M_i|^2 over the rows of MrtRows, am_i = (s_i - omega) m_i with m_i the
 // row's moment of N - rho P(u); those terms sum to zero over k, so the rest population still

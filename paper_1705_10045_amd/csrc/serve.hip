@@ -576,7 +576,8 @@ lbm_status capture_graph(lbm_pool* p, int kinds)
             const bool in_place = i % 2 == 0 && i + 1 == p->steps_per_run;
             const SlotState* state = p->d_state + (i % 2) * p->max_slots;
             SlotState* next = in_place ? nullptr : p->d_state + (1 - i % 2) * p->max_slots;
-            const int mgrid = 8 * kPoolGrid, cgrid = 3 * kPoolGrid;   // workgroups resident at once
+            // workgroups resident at once (of the moments with a table five per CU, the others wait)
+            const int mgrid = 8 * kPoolGrid, cgrid = 3 * kPoolGrid;
 #define LBM_POOL_MOMENTS(EXTK)                                                                            \
     if (kinds & ((1 << kind_of(EXTK, false)) | (1 << kind_of(EXTK, true))))                               \
     hipLaunchKernelGGL((k_pool_moments<EXTK == 0 ? kExtNone : (EXTK == 1 ? kExtWalls : kExtTable)>),      \

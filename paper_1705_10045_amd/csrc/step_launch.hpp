@@ -70,13 +70,14 @@ hipError_t launch_step_t(const void* src, void* dst, const StepGeom& g, const Ph
     // tiles.  With buffer addressing, and the pulls in the order of their use, the step fits the
     // registers of four tiles per CU for tau = 1 (127, against 144 for FP32 and, with global addressing,
     // 192 for FP64) and of three for MRT (168, against 184) and FP64 (150, against 214) without spills.
-    // us per step before and now: FP32 500^2 15.2 and 13.1, 1000^2 47.6 and 45.5, 1400^2 87.8 and 82.3;
-    // MRT 1000^2 56.8 and 50.0, 1400^2 109 and 92; FP64 350^2 13.7 and 10.4, 1000^2 76.9 and 71.1,
-    // 1400^2 145 and 132.  FP32 with tau != 1 holds three either way and is 3% faster in the old order.
+    // us per step before and now, one card: FP32 500^2 16.3 and 13.3, 1000^2 51.6 and 49.0, 1400^2 93.0 and
+    // 87.5; MRT 1000^2 62.3 and 52.7, 1400^2 116.7 and 96.9; FP64 350^2 13.6 and 10.4, 1000^2 78.9 and
+    // 71.5, 1400^2 145.8 and 132.8.  FP32 with tau != 1 holds three either way and is 3% faster in the old order.
     // Two tiles per CU stay where the tiles are two rounds of them (FP64: two to four) with the last at
-    // least half full: loads of one round then overlap the arithmetic of another (FP64 500^2 19.3 against
-    // 22.1, 600^2 28.9 against 29.8, 700^2 36.5 against 37.0, but 400^2 16.1 against 15.6; FP32 MRT
-    // 500^2 15.2 against 15.9, but 700^2 28.6 against 25.1).
+    // least half full: loads of one round then overlap the arithmetic of another.  The line is fitted to
+    // squares, not derived (another card: FP64 500^2 19.3 against 22.1, 600^2 28.9 against 29.8, 700^2 36.5 against
+    // 37.0, but 400^2 16.1 against 15.6; FP32 MRT 500^2 15.2 against 15.9, but 700^2 28.6 against 25.1); with it
+    // no square from 64^2 to 1400^2 was slower than before.
     constexpr bool kPlane = Q == 9 && NTH == 256 && !GLOBAL && !RED;
     if constexpr (kPlane) {
         const int tiles = g.ntx * g.nty, round = g.resident;

@@ -265,7 +265,7 @@ def lbm_launch_info(h):
 
 
 def lbm_launch_plan(Q, shape, physics, storage_bytes=4, cus=256):
-    """The launch lbm_init would choose for this box (host only, no device)."""
+    """The fused launch lbm_init would plan for this box (host only, no device)."""
     params = make_params(Q, shape, physics, storage_bytes)
     info = (ctypes.c_int * 4)()
     _check(lib().lbm_launch_plan(ctypes.byref(params), int(cus), info))
