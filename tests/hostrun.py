@@ -14,6 +14,7 @@ import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
+_DIR = tempfile.TemporaryDirectory(prefix="lbm_fake_hip_")
 
 _PRELUDE = r'''
 import ctypes, json, re, sys
@@ -45,7 +46,7 @@ def result(value):
 
 @functools.lru_cache(maxsize=1)
 def _runtime():
-    out = os.path.join(tempfile.mkdtemp(prefix="lbm_fake_hip_"), "libamdhip64.so")
+    out = os.path.join(_DIR.name, "libamdhip64.so")
     subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-Wall", "-Wl,-soname,libamdhip64.so.7",
                     "-Wl,--version-script," + os.path.join(HERE, "fake_hip.map"), "-o", out,
                     os.path.join(HERE, "fake_hip.c"), "-lpthread"], check=True)
